@@ -266,6 +266,7 @@ int permutation_partition(int64_t d, int32_t K, uint64_t seed, int64_t* offsets_
     a.d = d;
     a.K = K;
     a.half_bits = feistel_half_bits(d);
+    a.k_over_d = (double)K / (double)d;
     a.bucket = reinterpret_cast<uint8_t*>(ws);
     a.counts = reinterpret_cast<uint32_t*>(ws + L.off_counts);
     a.pos = reinterpret_cast<int64_t*>(ws + L.off_pos);

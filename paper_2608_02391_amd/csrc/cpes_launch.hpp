@@ -100,6 +100,7 @@ struct PartitionArgs {
     int64_t d;
     int32_t K;
     int32_t half_bits;      // h: the Feistel works on 2h bits
+    double k_over_d;        // K / d, rounded
     uint8_t* bucket;        // workspace: bucket of every element
     uint32_t* counts;       // workspace: counts[k * n_tiles + tile]
     int64_t* pos;           // workspace: exclusive positions, same layout
@@ -108,10 +109,10 @@ struct PartitionArgs {
     int64_t* index;         // output map (int64), or
     uint32_t* index32;      // output map (uint32, d <= 2^32)
     int32_t* status;
+    uint16_t* tables;       // round-function tables of a large partition, in the output map
 };
 
-// Tile of the permutation partition: one wave handles kTileItems x 64
-// consecutive elements.
+// Tile of the permutation partition: kTileItems x 64 consecutive elements.
 constexpr int kTileItems = 32;
 constexpr int64_t kTile = 64 * kTileItems;
 constexpr int kScanChunk = 4096;        // scan entries per workgroup

@@ -104,24 +104,6 @@ int check_sigma(float sigma, const char* fn)
     return CPES_OK;
 }
 
-// Whether the 16-byte vector path applies: every unit's vectors are aligned.
-// Element maps are read one entry per lane, and the weights they address one
-// element at a time, so only the side buffer's alignment matters for them.
-bool vector_ok(const void* w, int dtype, const cpes_subspace* s, const void* aux, bool aux_is_master)
-{
-    if (s->index && s->chunk) {
-        if (!aligned16(w)) return false;                    // chunk starts are multiples of 8 elements
-    } else if (s->index || s->index32) {
-        // nothing: the map kernels take any map offset
-    } else {
-        const char* base = static_cast<const char*>(w) + (size_t)s->offset * elem_size(dtype);
-        if (!aligned16(base)) return false;
-    }
-    if (aux && !aligned16(aux)) return false;
-    (void)aux_is_master;
-    return true;
-}
-
 cpes::StreamArgs stream_args(void* w, int64_t numel, const cpes_subspace* s, const void* aux, uint64_t seed,
                              float scale)
 {
@@ -311,9 +293,8 @@ int host_backup_copy(void* w_dev, int64_t numel, int dtype, const cpes_subspace*
     }
     // index-map or chunked: the copy kernels address the pinned buffer directly
     const cpes::StreamArgs a = stream_args(w_dev, numel, s, host_dev, 0, 0.0f);
-    const bool vec = vector_ok(w_dev, dtype, s, host_dev, false);
-    if (to_host) return hip_status(cpes::launch_backup_copy(dtype, addr_mode(s), vec, a, st), fn);
-    return hip_status(cpes::launch_restore_copy(dtype, addr_mode(s), vec, a, st), fn);
+    if (to_host) return hip_status(cpes::launch_backup_copy(dtype, addr_mode(s), a, st), fn);
+    return hip_status(cpes::launch_restore_copy(dtype, addr_mode(s), a, st), fn);
 }
 
 }  // namespace
@@ -482,9 +463,8 @@ int cpes_perturb(void* w_dev, int64_t numel, int dtype, const cpes_subspace* s, 
     if (s->length == 0) return CPES_OK;
     const float scale = sign > 0 ? sigma : -sigma;
     const void* aux = aux_mode == CPES_AUX_NONE ? nullptr : aux_dev;
-    const bool vec = vector_ok(w_dev, dtype, s, aux, aux_mode == CPES_AUX_MASTER);
     const cpes::StreamArgs a = stream_args(w_dev, numel, s, aux, seed, scale);
-    return hip_status(cpes::launch_perturb(dtype, aux_mode, addr_mode(s), vec, a, (hipStream_t)stream), fn);
+    return hip_status(cpes::launch_perturb(dtype, aux_mode, addr_mode(s), a, (hipStream_t)stream), fn);
 }
 
 int cpes_restore(void* w_dev, int64_t numel, int dtype, const cpes_subspace* s, float sigma, uint64_t seed,
@@ -509,12 +489,11 @@ int cpes_restore(void* w_dev, int64_t numel, int dtype, const cpes_subspace* s, 
     if (aux_mode == CPES_AUX_NONE) {
         const float scale = sign > 0 ? -sigma : sigma;
         const cpes::StreamArgs a = stream_args(w_dev, numel, s, nullptr, seed, scale);
-        return hip_status(cpes::launch_perturb(dtype, cpes::kAuxNone, addr, vector_ok(w_dev, dtype, s, nullptr, false), a, st), fn);
+        return hip_status(cpes::launch_perturb(dtype, cpes::kAuxNone, addr, a, st), fn);
     }
     const cpes::StreamArgs a = stream_args(w_dev, numel, s, aux_dev, seed, 0.0f);
-    const bool vec = vector_ok(w_dev, dtype, s, aux_dev, aux_mode == CPES_AUX_MASTER);
-    if (aux_mode == CPES_AUX_SNAPSHOT) return hip_status(cpes::launch_restore_copy(dtype, addr, vec, a, st), fn);
-    return hip_status(cpes::launch_restore_master(addr, vec, a, st), fn);
+    if (aux_mode == CPES_AUX_SNAPSHOT) return hip_status(cpes::launch_restore_copy(dtype, addr, a, st), fn);
+    return hip_status(cpes::launch_restore_master(addr, a, st), fn);
 }
 
 int cpes_backup_to_host(const void* w_dev, int64_t numel, int dtype, const cpes_subspace* s, void* backup_host,
@@ -542,8 +521,7 @@ int cpes_backup(const void* w_dev, int64_t numel, int dtype, const cpes_subspace
     if (!backup_dev) return fail(CPES_ERR_INVALID_ARGUMENT, "%s: backup pointer is null", fn);
     if (s->length == 0) return CPES_OK;
     const cpes::StreamArgs a = stream_args(const_cast<void*>(w_dev), numel, s, backup_dev, 0, 0.0f);
-    const bool vec = vector_ok(w_dev, dtype, s, backup_dev, false);
-    return hip_status(cpes::launch_backup_copy(dtype, addr_mode(s), vec, a, (hipStream_t)stream), fn);
+    return hip_status(cpes::launch_backup_copy(dtype, addr_mode(s), a, (hipStream_t)stream), fn);
 }
 
 int cpes_stage_master(const void* w_dev, int64_t numel, int dtype, const cpes_subspace* s, float* master_dev,
@@ -555,9 +533,8 @@ int cpes_stage_master(const void* w_dev, int64_t numel, int dtype, const cpes_su
     if (rc) return rc;
     if (!master_dev) return fail(CPES_ERR_INVALID_ARGUMENT, "%s: master_dev is null", fn);
     if (s->length == 0) return CPES_OK;
-    const bool vec = vector_ok(w_dev, dtype, s, master_dev, true);
     const cpes::StreamArgs a = stream_args(const_cast<void*>(w_dev), numel, s, master_dev, 0, 0.0f);
-    return hip_status(cpes::launch_stage_master(dtype, addr_mode(s), vec, a, (hipStream_t)stream), fn);
+    return hip_status(cpes::launch_stage_master(dtype, addr_mode(s), a, (hipStream_t)stream), fn);
 }
 
 int cpes_normalize_rewards(const float* r_dev, int32_t n, int mode, const int32_t* group_dev, int32_t n_groups,
@@ -634,8 +611,7 @@ int cpes_update(void* w_dev, int64_t numel, int dtype, const cpes_subspace* s, f
     a.n_streams = n_streams;
     a.chunk_shift = s->chunk ? log2_exact(s->chunk) : 0;
     a.noise0 = s->noise_offset;
-    const bool vec = vector_ok(w_dev, dtype, s, master_dev, true);
-    return hip_status(cpes::launch_update(dtype, master_dev != nullptr, addr_mode(s), vec, a, (hipStream_t)stream), fn);
+    return hip_status(cpes::launch_update(dtype, master_dev != nullptr, addr_mode(s), a, (hipStream_t)stream), fn);
 }
 
 }  // extern "C"
@@ -723,11 +699,6 @@ int update_step_impl(void* w_dev, int64_t numel, int dtype, int32_t K, const int
         a.length[k] = len;
         const int64_t units = (len + N - 1) / N;
         if (count[k] > 0) tiles += (units + 63) / 64;   // subspaces without members are left alone
-        const void* first = chunk ? w_dev
-                          : index_dev ? (const void*)(static_cast<const char*>(index_dev) +
-                                                      (size_t)offsets_host[k] * (idx32 ? 4 : 8))
-                                      : (const void*)(static_cast<const char*>(w_dev) + (size_t)offsets_host[k] * elem_size(dtype));
-        if (aligned16(first)) a.vec_mask |= 1u << k;
     }
     a.chunk_shift = chunk ? log2_exact(chunk) : 0;
     a.w = w_dev;
@@ -783,8 +754,7 @@ int cpes_fill_normal(void* w_dev, int64_t n, int dtype, uint64_t seed, uint32_t 
     if (rc) return rc;
     if (n == 0) return CPES_OK;
     if (!w_dev) return fail(CPES_ERR_INVALID_ARGUMENT, "%s: w is null", fn);
-    return hip_status(cpes::launch_fill_normal(dtype, w_dev, n, seed, domain, stddev, aligned16(w_dev),
-                                               (hipStream_t)stream), fn);
+    return hip_status(cpes::launch_fill_normal(dtype, w_dev, n, seed, domain, stddev, (hipStream_t)stream), fn);
 }
 
 int cpes_debug_philox(uint64_t seed, uint32_t domain, uint64_t q0, int64_t nblocks, uint32_t* out_dev, void* stream)

@@ -4,9 +4,8 @@
 // "units" of consecutive subspace positions: 8 for bf16 weights (one 16-byte
 // vector, two Philox blocks) and 4 for fp32 weights (one 16-byte vector, one
 // Philox block), one unit per thread at a time.  A wave therefore moves 1 KiB
-// per vector access, fully coalesced.  Units whose 16-byte vectors are not
-// aligned (an odd subspace offset, an odd map entry) and the ragged tail take
-// an element-by-element path with the same arithmetic.  Subspaces are ranges,
+// per vector access, fully coalesced.  The ragged tail takes an
+// element-by-element path with the same arithmetic.  Subspaces are ranges,
 // int64 or uint32 element maps, or chunk lists.  Noise never leaves registers.
 #include <algorithm>
 #include <type_traits>
@@ -48,30 +47,45 @@ __device__ __forceinline__ void unit_normals<8>(uint32_t k0, uint32_t k1, uint64
 // parameters and up) then streams past them instead of evicting lines that
 // are never reused, which measured 3-5 % faster on such copies; copies of a
 // few tens of MB keep the default policy, since they run from cache.
+//
+// The vectors need no more than their elements' alignment: an even split of a
+// model whose size is no multiple of 8 K starts its subspaces at any element,
+// and gfx950 takes 16-byte accesses at any address (a wave's 1 KiB then spans
+// nine 128-byte lines instead of eight).  33,333,335 bf16 weights from an odd
+// element on: restore 54 -> 17.6 us, perturbation 69 -> 38 us against an
+// element path, 17.3 and 37.5 us from an aligned one.
 typedef unsigned int V4u __attribute__((ext_vector_type(4)));
 typedef float V4f __attribute__((ext_vector_type(4)));
+typedef V4f V4fAnywhere __attribute__((aligned(4)));
+typedef unsigned int V2u __attribute__((ext_vector_type(2)));
+typedef V2u V2uAnywhere __attribute__((aligned(2)));
+template <typename T> struct Vec16;
+template <> struct Vec16<uint16_t> { typedef V4u type __attribute__((aligned(2))); };
+template <> struct Vec16<float> { typedef V4u type __attribute__((aligned(4))); };
 
 template <typename T, bool NT = false>
 __device__ __forceinline__ void load_vec(const T* p, T v[UnitOf<T>::n])
 {
-    const V4u* q = reinterpret_cast<const V4u*>(p);
+    typedef typename Vec16<T>::type V;
+    const V* q = reinterpret_cast<const V*>(p);
     *reinterpret_cast<V4u*>(v) = NT ? __builtin_nontemporal_load(q) : *q;
 }
 template <typename T, bool NT = false>
 __device__ __forceinline__ void store_vec(T* p, const T v[UnitOf<T>::n])
 {
+    typedef typename Vec16<T>::type V;
     const V4u x = *reinterpret_cast<const V4u*>(v);
     if (NT)
-        __builtin_nontemporal_store(x, reinterpret_cast<V4u*>(p));
+        __builtin_nontemporal_store(x, reinterpret_cast<V*>(p));
     else
-        *reinterpret_cast<V4u*>(p) = x;
+        *reinterpret_cast<V*>(p) = x;
 }
 template <int N, bool NT = false>
 __device__ __forceinline__ void load_f32s(const float* p, float v[N])
 {
 #pragma unroll
     for (int h = 0; h < N / 4; ++h) {
-        const V4f* q = reinterpret_cast<const V4f*>(p) + h;
+        const V4fAnywhere* q = reinterpret_cast<const V4fAnywhere*>(p) + h;
         const V4f x = NT ? __builtin_nontemporal_load(q) : *q;
         v[4 * h + 0] = x[0]; v[4 * h + 1] = x[1]; v[4 * h + 2] = x[2]; v[4 * h + 3] = x[3];
     }
@@ -83,9 +97,9 @@ __device__ __forceinline__ void store_f32s(float* p, const float v[N])
     for (int h = 0; h < N / 4; ++h) {
         const V4f x = {v[4 * h + 0], v[4 * h + 1], v[4 * h + 2], v[4 * h + 3]};
         if (NT)
-            __builtin_nontemporal_store(x, reinterpret_cast<V4f*>(p) + h);
+            __builtin_nontemporal_store(x, reinterpret_cast<V4fAnywhere*>(p) + h);
         else
-            reinterpret_cast<V4f*>(p)[h] = x;
+            reinterpret_cast<V4fAnywhere*>(p)[h] = x;
     }
 }
 __device__ __forceinline__ int64_t grid_stride() { return (int64_t)gridDim.x * blockDim.x; }
@@ -167,19 +181,14 @@ __device__ __forceinline__ bool unit_base(const int64_t* index, int64_t offset, 
 }
 
 // Drive a streaming kernel: every full unit goes through `vec_body` (16-byte
-// accesses; only when the subspace's vectors are aligned) or `scalar_body`
-// (element accesses) in a branch-free grid-stride loop, so that per-launch
-// invariants (polynomial constants, key schedule) stay hoisted; the ragged
-// last unit, if any, is done once by thread 0 with `scalar_body`.
-template <int N, bool VEC, typename VecBody, typename ScalarBody>
+// accesses) in a branch-free grid-stride loop, so that per-launch invariants
+// (polynomial constants, key schedule) stay hoisted; the ragged last unit, if
+// any, is done once by thread 0 with `scalar_body` (element accesses).
+template <int N, typename VecBody, typename ScalarBody>
 __device__ __forceinline__ void for_each_unit(int64_t length, VecBody&& vec_body, ScalarBody&& scalar_body)
 {
     const int64_t full = length / N;
-    if (VEC) {
-        for (int64_t u = global_tid(); u < full; u += grid_stride()) vec_body(u);
-    } else {
-        for (int64_t u = global_tid(); u < full; u += grid_stride()) scalar_body(u);
-    }
+    for (int64_t u = global_tid(); u < full; u += grid_stride()) vec_body(u);
     if (full * N < length && global_tid() == 0) scalar_body(full);
 }
 
@@ -188,7 +197,7 @@ __device__ __forceinline__ void for_each_unit(int64_t length, VecBody&& vec_body
 // the snapshot first), the fp32 master, or an existing backup.  Also serves
 // replay restore with scale = -sign * sigma.  Contiguous and chunked
 // subspaces; index maps take k_perturb_map below.
-template <typename T, int AUX, int ADDR, bool VEC>
+template <typename T, int AUX, int ADDR>
 __global__ __launch_bounds__(kBlock) void k_perturb(StreamArgs a)
 {
     constexpr int N = UnitOf<T>::n;
@@ -245,12 +254,12 @@ __global__ __launch_bounds__(kBlock) void k_perturb(StreamArgs a)
         for (int e = 0; e < N; ++e) out[e] = from_f32<T>(__builtin_fmaf(a.scale, z[e], src[e]));
         store_vec<T>(w + base, out);
     };
-    for_each_unit<N, VEC>(a.length, vec_body, scalar_body);
+    for_each_unit<N>(a.length, vec_body, scalar_body);
 }
 
 // --------------------------------------------------------------- restores --
 // Snapshot restore: w[p(j)] = snap[j], a bit copy.
-template <typename T, bool NT, int ADDR, bool VEC>
+template <typename T, bool NT, int ADDR>
 __global__ __launch_bounds__(kBlock) void k_restore_copy(StreamArgs a)
 {
     constexpr int N = UnitOf<T>::n;
@@ -276,12 +285,12 @@ __global__ __launch_bounds__(kBlock) void k_restore_copy(StreamArgs a)
         load_vec<T, NT>(snap + j0, v);
         store_vec<T, NT>(w + base, v);
     };
-    for_each_unit<N, VEC>(a.length, vec_body, scalar_body);
+    for_each_unit<N>(a.length, vec_body, scalar_body);
 }
 
 // Backup copy: backup[j] = w[p(j)] (bit copy), for backups taken apart from a
 // perturbation, in device memory or in pinned host memory.
-template <typename T, bool NT, int ADDR, bool VEC>
+template <typename T, bool NT, int ADDR>
 __global__ __launch_bounds__(kBlock) void k_backup_copy(StreamArgs a)
 {
     constexpr int N = UnitOf<T>::n;
@@ -307,11 +316,11 @@ __global__ __launch_bounds__(kBlock) void k_backup_copy(StreamArgs a)
         load_vec<T, NT>(w + base, v);
         store_vec<T, NT>(backup + j0, v);
     };
-    for_each_unit<N, VEC>(a.length, vec_body, scalar_body);
+    for_each_unit<N>(a.length, vec_body, scalar_body);
 }
 
 // Master restore (bf16 weights): w[p(j)] = rne_bf16(master[j]).
-template <bool NT, int ADDR, bool VEC>
+template <bool NT, int ADDR>
 __global__ __launch_bounds__(kBlock) void k_restore_master(StreamArgs a)
 {
     constexpr int N = 8;
@@ -340,11 +349,11 @@ __global__ __launch_bounds__(kBlock) void k_restore_master(StreamArgs a)
         for (int e = 0; e < N; ++e) v[e] = f32_to_bf16(m[e]);
         store_vec<uint16_t, NT>(w + base, v);
     };
-    for_each_unit<N, VEC>(a.length, vec_body, scalar_body);
+    for_each_unit<N>(a.length, vec_body, scalar_body);
 }
 
 // Master staging: master[j] = f32(w[p(j)]).
-template <typename T, bool NT, int ADDR, bool VEC>
+template <typename T, bool NT, int ADDR>
 __global__ __launch_bounds__(kBlock) void k_stage_master(StreamArgs a)
 {
     constexpr int N = UnitOf<T>::n;
@@ -373,7 +382,7 @@ __global__ __launch_bounds__(kBlock) void k_stage_master(StreamArgs a)
         for (int e = 0; e < N; ++e) m[e] = to_f32<T>(v[e]);
         store_f32s<N, NT>(master + j0, m);
     };
-    for_each_unit<N, VEC>(a.length, vec_body, scalar_body);
+    for_each_unit<N>(a.length, vec_body, scalar_body);
 }
 
 // ----------------------------------------------------------------- update --
@@ -411,7 +420,7 @@ __device__ __forceinline__ void accumulate_streams(const uint32_t* seed_lo, cons
     }
 }
 
-template <typename T, bool MASTER, int ADDR, bool VEC>
+template <typename T, bool MASTER, int ADDR>
 __global__ __launch_bounds__(kBlock) void k_update(UpdateArgs a)
 {
     constexpr int N = MASTER ? 8 : UnitOf<T>::n;
@@ -470,7 +479,7 @@ __global__ __launch_bounds__(kBlock) void k_update(UpdateArgs a)
         }
         store_vec<T>(w + base, out);
     };
-    for_each_unit<N, VEC>(a.length, vec_body, scalar_body);
+    for_each_unit<N>(a.length, vec_body, scalar_body);
 }
 
 // ------------------------------------------------------- index-map kernels --
@@ -594,12 +603,12 @@ __device__ __forceinline__ void lanes_to_units(T* buf, int lane, const T in[N], 
 }
 
 // Unit-wise side buffer access at positions j0 .. j0 + N - 1, bounded by
-// `length` (a tile may end inside a unit); 16-byte vectors when VEC and the
-// unit is whole.
-template <typename T, bool VEC, int N>
+// `length` (a tile may end inside a unit); 16-byte vectors when the unit is
+// whole.
+template <typename T, int N>
 __device__ __forceinline__ void load_unit(const T* p, int64_t j0, int64_t length, T v[N])
 {
-    if (VEC && j0 + N <= length) {
+    if (j0 + N <= length) {
         if (sizeof(T) * N == 16) {
             load_vec<T>(p + j0, v);
         } else {
@@ -610,10 +619,10 @@ __device__ __forceinline__ void load_unit(const T* p, int64_t j0, int64_t length
         for (int e = 0; e < N; ++e) v[e] = j0 + e < length ? p[j0 + e] : T(0);
     }
 }
-template <typename T, bool VEC, int N>
+template <typename T, int N>
 __device__ __forceinline__ void store_unit(T* p, int64_t j0, int64_t length, const T v[N])
 {
-    if (VEC && j0 + N <= length) {
+    if (j0 + N <= length) {
         if (sizeof(T) * N == 16) {
             store_vec<T>(p + j0, v);
         } else {
@@ -627,7 +636,7 @@ __device__ __forceinline__ void store_unit(T* p, int64_t j0, int64_t length, con
 }
 
 // Perturbation through a map (see k_perturb for the arithmetic).
-template <typename T, int AUX, bool VEC, int ADDR>
+template <typename T, int AUX, int ADDR>
 __global__ __launch_bounds__(kBlock) void k_perturb_map(StreamArgs a)
 {
     constexpr int N = UnitOf<T>::n;
@@ -643,16 +652,16 @@ __global__ __launch_bounds__(kBlock) void k_perturb_map(StreamArgs a)
         const bool all_valid = tile_entries<ADDR, N>(a.index, a.offset, a.length, a.numel, t0, lane, idx);
         float src[N];
         if (AUX == kAuxMaster) {
-            load_unit<float, VEC, N>(static_cast<const float*>(a.aux), j0, a.length, src);
+            load_unit<float, N>(static_cast<const float*>(a.aux), j0, a.length, src);
         } else {
             T old[N];
             if (AUX == kAuxBackup) {
-                load_unit<T, VEC, N>(static_cast<const T*>(a.aux), j0, a.length, old);
+                load_unit<T, N>(static_cast<const T*>(a.aux), j0, a.length, old);
             } else {
                 T g[N];
                 gather_lanes<T, N>(w, idx, all_valid, g);
                 lanes_to_units<T, N>(buf, lane, g, old);
-                if (AUX == kAuxSnapshot) store_unit<T, VEC, N>(static_cast<T*>(a.aux), j0, a.length, old);
+                if (AUX == kAuxSnapshot) store_unit<T, N>(static_cast<T*>(a.aux), j0, a.length, old);
             }
 #pragma unroll
             for (int e = 0; e < N; ++e) src[e] = to_f32<T>(old[e]);
@@ -892,7 +901,7 @@ __global__ __launch_bounds__(kBlock) void k_restore_dense(StreamArgs a)
 // are stored one by one, as the neighbour stores its own entries there, so a
 // line written whole has no other writer.  Lane l takes the tile's positions
 // t0 + 4 l .. t0 + 4 l + 3, which are one Philox block of noise, and moves
-// the map and the side buffers as 8- or 16-byte vectors where aligned.  The
+// the map and the side buffers as 8- or 16-byte vectors.  The
 // perturbation is that of Eq. (8) on a subspace of the partition of Eq. (7).
 // (Restores tiled this way, with no noise to generate, measured a few per
 // cent slower than the spill kernel above, which they therefore keep.)
@@ -916,21 +925,22 @@ __device__ __forceinline__ DenseTile edge_tile(const int64_t* index, int64_t off
 }
 
 // Entries p .. p + 3 of the map (n of them exist; -1 for the others and for
-// entries outside [0, numel)); vector loads when `vec` (16-byte aligned).
+// entries outside [0, numel)).
 template <int ADDR>
-__device__ __forceinline__ void map_entries4(const int64_t* index, int64_t p, int64_t n, bool vec, int64_t numel,
+__device__ __forceinline__ void map_entries4(const int64_t* index, int64_t p, int64_t n, int64_t numel,
                                              int64_t idx[4])
 {
-    if (vec && n >= 4) {
+    if (n >= 4) {
+        typedef Vec16<float>::type V;
         if (ADDR == kGather) {
-            const V4u x = *reinterpret_cast<const V4u*>(index + p);
-            const V4u y = *reinterpret_cast<const V4u*>(index + p + 2);
+            const V4u x = *reinterpret_cast<const V*>(index + p);
+            const V4u y = *reinterpret_cast<const V*>(index + p + 2);
             idx[0] = (int64_t)(((uint64_t)x[1] << 32) | x[0]);
             idx[1] = (int64_t)(((uint64_t)x[3] << 32) | x[2]);
             idx[2] = (int64_t)(((uint64_t)y[1] << 32) | y[0]);
             idx[3] = (int64_t)(((uint64_t)y[3] << 32) | y[2]);
         } else {
-            const V4u x = *reinterpret_cast<const V4u*>(reinterpret_cast<const uint32_t*>(index) + p);
+            const V4u x = *reinterpret_cast<const V*>(reinterpret_cast<const uint32_t*>(index) + p);
 #pragma unroll
             for (int e = 0; e < 4; ++e) idx[e] = (int64_t)x[e];
         }
@@ -977,9 +987,6 @@ __global__ __launch_bounds__(kDenseBlock, 6) void k_perturb_dense(StreamArgs a)
     const int lane = threadIdx.x & 63;
     uint16_t* buf = win[threadIdx.x / 64];
     uint16_t* w = static_cast<uint16_t*>(a.w);
-    constexpr uint64_t kEntry = ADDR == kGather ? 8 : 4;
-    const bool vmap = (((uintptr_t)a.index + (uint64_t)a.offset * kEntry) & 15) == 0;
-    const bool vaux = ((uintptr_t)a.aux & (AUX == kAuxMaster ? 15 : 7)) == 0;
     const int64_t tiles = (a.length + kDenseTile - 1) / kDenseTile;
     const int64_t waves = (int64_t)gridDim.x * (kDenseBlock / 64);
     for (int64_t t = (int64_t)blockIdx.x * (kDenseBlock / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x / 64); t < tiles;
@@ -988,13 +995,13 @@ __global__ __launch_bounds__(kDenseBlock, 6) void k_perturb_dense(StreamArgs a)
         const int64_t j0 = d.t0 + 4 * lane;
         const bool whole = j0 + 4 <= a.length;
         int64_t idx[4];
-        map_entries4<ADDR>(a.index, a.offset + j0, a.length - j0, vmap, a.numel, idx);
+        map_entries4<ADDR>(a.index, a.offset + j0, a.length - j0, a.numel, idx);
         float src[4];
         if (AUX == kAuxBackup) {
             const uint16_t* b = static_cast<const uint16_t*>(a.aux) + j0;
             uint16_t o[4];
-            if (vaux && whole) {
-                *reinterpret_cast<uint2*>(o) = *reinterpret_cast<const uint2*>(b);
+            if (whole) {
+                *reinterpret_cast<V2u*>(o) = *reinterpret_cast<const V2uAnywhere*>(b);
             } else {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) o[e] = j0 + e < a.length ? b[e] : (uint16_t)0;
@@ -1003,7 +1010,7 @@ __global__ __launch_bounds__(kDenseBlock, 6) void k_perturb_dense(StreamArgs a)
             for (int e = 0; e < 4; ++e) src[e] = bf16_to_f32(o[e]);
         } else if (AUX == kAuxMaster) {
             const float* m = static_cast<const float*>(a.aux) + j0;
-            if (vaux && whole) {
+            if (whole) {
                 load_f32s<4>(m, src);
             } else {
 #pragma unroll
@@ -1028,8 +1035,8 @@ __global__ __launch_bounds__(kDenseBlock, 6) void k_perturb_dense(StreamArgs a)
             for (int e = 0; e < 4; ++e) o[e] = in[e] ? buf[idx[e] - base] : idx[e] >= 0 ? w[idx[e]] : (uint16_t)0;
             if (AUX == kAuxSnapshot) {
                 uint16_t* snap = static_cast<uint16_t*>(a.aux) + j0;
-                if (vaux && whole) {
-                    *reinterpret_cast<uint2*>(snap) = *reinterpret_cast<const uint2*>(o);
+                if (whole) {
+                    *reinterpret_cast<V2uAnywhere*>(snap) = *reinterpret_cast<const V2u*>(o);
                 } else {
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
@@ -1047,7 +1054,7 @@ __global__ __launch_bounds__(kDenseBlock, 6) void k_perturb_dense(StreamArgs a)
 }
 
 // Update through a map (see k_update for the arithmetic).
-template <typename T, bool MASTER, bool VEC, int ADDR>
+template <typename T, bool MASTER, int ADDR>
 __global__ __launch_bounds__(kBlock) void k_update_map(UpdateArgs a)
 {
     constexpr int N = UnitOf<T>::n;   // a master update has bf16 weights: N = 8
@@ -1070,13 +1077,13 @@ __global__ __launch_bounds__(kBlock) void k_update_map(UpdateArgs a)
         T out[N], v[N];
         if (MASTER) {
             float m[N];
-            load_unit<float, VEC, N>(a.master, j0, a.length, m);
+            load_unit<float, N>(a.master, j0, a.length, m);
 #pragma unroll
             for (int e = 0; e < N; ++e) {
                 m[e] = __builtin_fmaf(a.step, acc[e], m[e]);
                 out[e] = from_f32<T>(m[e]);
             }
-            store_unit<float, VEC, N>(a.master, j0, a.length, m);
+            store_unit<float, N>(a.master, j0, a.length, m);
         } else {
             T old[N];
             lanes_to_units<T, N>(buf, lane, g, old);
@@ -1135,7 +1142,7 @@ __global__ __launch_bounds__(kBlock) void k_update_step(StepArgs a)
         }
         if (j0 >= len) continue;
         int64_t base = 0;
-        const bool vec = ((a.vec_mask >> k) & 1u) && j0 + N <= len &&
+        const bool vec = j0 + N <= len &&
                          unit_base<ADDR>(a.index, off, a.numel, a.chunk_shift, j0, N, base);
         float acc[N];
         accumulate_streams<N>(a.seed_lo, a.seed_hi, coef, st0, st1, (uint64_t)j0 >> 2, tb, acc);
@@ -1789,7 +1796,7 @@ __global__ __launch_bounds__(kBlock) void k_debug_normals(uint64_t seed, int64_t
 
 // Seeded normal fill: w[j] = cast(stddev * z_j), z_j the normal of position
 // j in stream (seed, domain).
-template <typename T, bool VEC>
+template <typename T>
 __global__ __launch_bounds__(kBlock) void k_fill_normal(T* w, int64_t n, uint64_t seed, uint32_t domain, float stddev)
 {
     constexpr int N = UnitOf<T>::n;
@@ -1814,7 +1821,7 @@ __global__ __launch_bounds__(kBlock) void k_fill_normal(T* w, int64_t n, uint64_
         }
     };
     const int64_t full = n / N;
-    for (int64_t u = global_tid(); u < full; u += grid_stride()) body(u, VEC);
+    for (int64_t u = global_tid(); u < full; u += grid_stride()) body(u, true);
     if (full * N < n && global_tid() == 0) body(full, false);
 }
 
@@ -1938,16 +1945,14 @@ int64_t map_threads(int64_t length)
     return (length + tile - 1) / tile * 64;
 }
 
-// Instantiate a streaming kernel for the addressing mode and vector flag;
-// element maps go to the map kernel MAPK instantiated with MARGS.
+// Instantiate a streaming kernel for the addressing mode; element maps go to
+// the map kernel MAPK instantiated with MARGS.
 #define CPES_DISPATCH(KERNEL, KARGS, MAPK, MARGS)                                                     \
     switch (addr) {                                                                                  \
     case kGather: return launch1d(MAPK<MARGS, kGather>, map_threads<T>(a.length), a, s, kMaxGrid); \
     case kGather32: return launch1d(MAPK<MARGS, kGather32>, map_threads<T>(a.length), a, s, kMaxGrid); \
-    case kChunk: return vec ? launch1d(KERNEL<KARGS, kChunk, true>, u, a, s, cap)                    \
-                            : launch1d(KERNEL<KARGS, kChunk, false>, u, a, s, cap);                  \
-    default: return vec ? launch1d(KERNEL<KARGS, kContig, true>, u, a, s, cap)                       \
-                        : launch1d(KERNEL<KARGS, kContig, false>, u, a, s, cap);                     \
+    case kChunk: return launch1d(KERNEL<KARGS, kChunk>, u, a, s, cap);                               \
+    default: return launch1d(KERNEL<KARGS, kContig>, u, a, s, cap);                                  \
     }
 #define CPES_COMMA ,
 
@@ -1958,7 +1963,7 @@ int64_t dense_threads(int64_t length)
 }
 
 template <typename T, int AUX>
-hipError_t perturb_t(int addr, bool vec, const StreamArgs& a, hipStream_t s)
+hipError_t perturb_t(int addr, const StreamArgs& a, hipStream_t s)
 {
     if (std::is_same<T, uint16_t>::value && a.dense) {
         const dim3 grid((unsigned)std::min<int64_t>(std::max<int64_t>((dense_threads(a.length) + kDenseBlock - 1) / kDenseBlock, 1),
@@ -1968,21 +1973,15 @@ hipError_t perturb_t(int addr, bool vec, const StreamArgs& a, hipStream_t s)
         if (addr == kGather || addr == kGather32) return hipGetLastError();
     }
     const int64_t u = units_of<T>(a.length), cap = kRngMaxGrid;
-    if (vec) {
-        CPES_DISPATCH(k_perturb, T CPES_COMMA AUX, k_perturb_map, T CPES_COMMA AUX CPES_COMMA true)
-    }
-    CPES_DISPATCH(k_perturb, T CPES_COMMA AUX, k_perturb_map, T CPES_COMMA AUX CPES_COMMA false)
+    CPES_DISPATCH(k_perturb, T CPES_COMMA AUX, k_perturb_map, T CPES_COMMA AUX)
 }
 
 template <typename T, bool MASTER>
-hipError_t update_t(int addr, bool vec, const UpdateArgs& a, hipStream_t s)
+hipError_t update_t(int addr, const UpdateArgs& a, hipStream_t s)
 {
     constexpr int N = MASTER ? 8 : UnitOf<T>::n;
     const int64_t u = (a.length + N - 1) / N, cap = kRngMaxGrid;
-    if (vec) {
-        CPES_DISPATCH(k_update, T CPES_COMMA MASTER, k_update_map, T CPES_COMMA MASTER CPES_COMMA true)
-    }
-    CPES_DISPATCH(k_update, T CPES_COMMA MASTER, k_update_map, T CPES_COMMA MASTER CPES_COMMA false)
+    CPES_DISPATCH(k_update, T CPES_COMMA MASTER, k_update_map, T CPES_COMMA MASTER)
 }
 
 // Copies whose source and destination together exceed the 256 MB last-level
@@ -1995,7 +1994,7 @@ inline bool streaming(int64_t length, int bytes_per_position)
 }
 
 template <typename T>
-hipError_t restore_copy_t(int addr, bool vec, const StreamArgs& a, hipStream_t s)
+hipError_t restore_copy_t(int addr, const StreamArgs& a, hipStream_t s)
 {
     if (std::is_same<T, uint16_t>::value && a.dense) {
         if (addr == kGather) return launch1d(k_restore_dense<kCopyRestore, kGather>, dense_threads(a.length), a, s, kMaxGrid);
@@ -2009,7 +2008,7 @@ hipError_t restore_copy_t(int addr, bool vec, const StreamArgs& a, hipStream_t s
 }
 
 template <typename T>
-hipError_t backup_copy_t(int addr, bool vec, const StreamArgs& a, hipStream_t s)
+hipError_t backup_copy_t(int addr, const StreamArgs& a, hipStream_t s)
 {
     const int64_t u = units_of<T>(a.length), cap = kMaxGrid;
     if (streaming(a.length, 2 * sizeof(T))) {
@@ -2019,7 +2018,7 @@ hipError_t backup_copy_t(int addr, bool vec, const StreamArgs& a, hipStream_t s)
 }
 
 template <typename T>
-hipError_t stage_master_t(int addr, bool vec, const StreamArgs& a, hipStream_t s)
+hipError_t stage_master_t(int addr, const StreamArgs& a, hipStream_t s)
 {
     const int64_t u = units_of<T>(a.length), cap = kMaxGrid;
     if (streaming(a.length, sizeof(T) + 4)) {
@@ -2028,7 +2027,7 @@ hipError_t stage_master_t(int addr, bool vec, const StreamArgs& a, hipStream_t s
     CPES_DISPATCH(k_stage_master, T CPES_COMMA false, k_copy_map, T CPES_COMMA kCopyStageMaster CPES_COMMA false)
 }
 
-hipError_t restore_master_t(int addr, bool vec, const StreamArgs& a, hipStream_t s)
+hipError_t restore_master_t(int addr, const StreamArgs& a, hipStream_t s)
 {
     using T = uint16_t;
     if (a.dense) {
@@ -2058,43 +2057,43 @@ hipError_t update_step_t(int addr, const StepArgs& a, hipStream_t s)
 
 }  // namespace
 
-hipError_t launch_perturb(int dtype, int aux, int addr, bool vec, const StreamArgs& a, hipStream_t s)
+hipError_t launch_perturb(int dtype, int aux, int addr, const StreamArgs& a, hipStream_t s)
 {
     if (dtype == 0) {
-        if (aux == kAuxSnapshot) return perturb_t<uint16_t, kAuxSnapshot>(addr, vec, a, s);
-        if (aux == kAuxMaster) return perturb_t<uint16_t, kAuxMaster>(addr, vec, a, s);
-        if (aux == kAuxBackup) return perturb_t<uint16_t, kAuxBackup>(addr, vec, a, s);
-        return perturb_t<uint16_t, kAuxNone>(addr, vec, a, s);
+        if (aux == kAuxSnapshot) return perturb_t<uint16_t, kAuxSnapshot>(addr, a, s);
+        if (aux == kAuxMaster) return perturb_t<uint16_t, kAuxMaster>(addr, a, s);
+        if (aux == kAuxBackup) return perturb_t<uint16_t, kAuxBackup>(addr, a, s);
+        return perturb_t<uint16_t, kAuxNone>(addr, a, s);
     }
-    if (aux == kAuxSnapshot) return perturb_t<float, kAuxSnapshot>(addr, vec, a, s);
-    if (aux == kAuxBackup) return perturb_t<float, kAuxBackup>(addr, vec, a, s);
-    return perturb_t<float, kAuxNone>(addr, vec, a, s);
+    if (aux == kAuxSnapshot) return perturb_t<float, kAuxSnapshot>(addr, a, s);
+    if (aux == kAuxBackup) return perturb_t<float, kAuxBackup>(addr, a, s);
+    return perturb_t<float, kAuxNone>(addr, a, s);
 }
 
-hipError_t launch_restore_copy(int dtype, int addr, bool vec, const StreamArgs& a, hipStream_t s)
+hipError_t launch_restore_copy(int dtype, int addr, const StreamArgs& a, hipStream_t s)
 {
-    return dtype == 0 ? restore_copy_t<uint16_t>(addr, vec, a, s) : restore_copy_t<float>(addr, vec, a, s);
+    return dtype == 0 ? restore_copy_t<uint16_t>(addr, a, s) : restore_copy_t<float>(addr, a, s);
 }
 
-hipError_t launch_backup_copy(int dtype, int addr, bool vec, const StreamArgs& a, hipStream_t s)
+hipError_t launch_backup_copy(int dtype, int addr, const StreamArgs& a, hipStream_t s)
 {
-    return dtype == 0 ? backup_copy_t<uint16_t>(addr, vec, a, s) : backup_copy_t<float>(addr, vec, a, s);
+    return dtype == 0 ? backup_copy_t<uint16_t>(addr, a, s) : backup_copy_t<float>(addr, a, s);
 }
 
-hipError_t launch_restore_master(int addr, bool vec, const StreamArgs& a, hipStream_t s)
+hipError_t launch_restore_master(int addr, const StreamArgs& a, hipStream_t s)
 {
-    return restore_master_t(addr, vec, a, s);
+    return restore_master_t(addr, a, s);
 }
 
-hipError_t launch_stage_master(int dtype, int addr, bool vec, const StreamArgs& a, hipStream_t s)
+hipError_t launch_stage_master(int dtype, int addr, const StreamArgs& a, hipStream_t s)
 {
-    return dtype == 0 ? stage_master_t<uint16_t>(addr, vec, a, s) : stage_master_t<float>(addr, vec, a, s);
+    return dtype == 0 ? stage_master_t<uint16_t>(addr, a, s) : stage_master_t<float>(addr, a, s);
 }
 
-hipError_t launch_update(int dtype, bool master, int addr, bool vec, const UpdateArgs& a, hipStream_t s)
+hipError_t launch_update(int dtype, bool master, int addr, const UpdateArgs& a, hipStream_t s)
 {
-    if (dtype == 0) return master ? update_t<uint16_t, true>(addr, vec, a, s) : update_t<uint16_t, false>(addr, vec, a, s);
-    return update_t<float, false>(addr, vec, a, s);
+    if (dtype == 0) return master ? update_t<uint16_t, true>(addr, a, s) : update_t<uint16_t, false>(addr, a, s);
+    return update_t<float, false>(addr, a, s);
 }
 
 hipError_t launch_update_step(int dtype, int addr, const StepArgs& a, hipStream_t s)
@@ -2102,19 +2101,14 @@ hipError_t launch_update_step(int dtype, int addr, const StepArgs& a, hipStream_
     return dtype == 0 ? update_step_t<uint16_t>(addr, a, s) : update_step_t<float>(addr, a, s);
 }
 
-hipError_t launch_fill_normal(int dtype, void* w, int64_t n, uint64_t seed, uint32_t domain, float stddev, bool vec,
+hipError_t launch_fill_normal(int dtype, void* w, int64_t n, uint64_t seed, uint32_t domain, float stddev,
                               hipStream_t s)
 {
     const dim3 grid((unsigned)grid_for(n / (dtype == 0 ? 8 : 4) + 1, kRngMaxGrid)), block(kBlock);
-    if (dtype == 0) {
-        uint16_t* p = static_cast<uint16_t*>(w);
-        if (vec) hipLaunchKernelGGL((k_fill_normal<uint16_t, true>), grid, block, 0, s, p, n, seed, domain, stddev);
-        else hipLaunchKernelGGL((k_fill_normal<uint16_t, false>), grid, block, 0, s, p, n, seed, domain, stddev);
-    } else {
-        float* p = static_cast<float*>(w);
-        if (vec) hipLaunchKernelGGL((k_fill_normal<float, true>), grid, block, 0, s, p, n, seed, domain, stddev);
-        else hipLaunchKernelGGL((k_fill_normal<float, false>), grid, block, 0, s, p, n, seed, domain, stddev);
-    }
+    if (dtype == 0)
+        hipLaunchKernelGGL(k_fill_normal<uint16_t>, grid, block, 0, s, static_cast<uint16_t*>(w), n, seed, domain, stddev);
+    else
+        hipLaunchKernelGGL(k_fill_normal<float>, grid, block, 0, s, static_cast<float*>(w), n, seed, domain, stddev);
     return hipGetLastError();
 }
 

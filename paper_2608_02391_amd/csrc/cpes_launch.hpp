@@ -73,7 +73,6 @@ struct StepArgs {
     int32_t n_members;
     int32_t n_streams;
     int32_t chunk_shift;
-    uint32_t vec_mask;                             // bit k: subspace k takes 16-byte vectors
     int64_t offset[kMaxStepSubspaces + 1];         // subspace k starts at position / map entry offset[k]
     int64_t length[kMaxStepSubspaces];             // and has length[k] positions
     int64_t tile_begin[kMaxStepSubspaces + 1];     // first wave tile of subspace k
@@ -117,14 +116,14 @@ constexpr int kTileItems = 32;
 constexpr int64_t kTile = 64 * kTileItems;
 constexpr int kScanChunk = 4096;        // scan entries per workgroup
 
-hipError_t launch_perturb(int dtype, int aux, int addr, bool vec, const StreamArgs& a, hipStream_t s);
-hipError_t launch_restore_copy(int dtype, int addr, bool vec, const StreamArgs& a, hipStream_t s);
-hipError_t launch_restore_master(int addr, bool vec, const StreamArgs& a, hipStream_t s);
-hipError_t launch_backup_copy(int dtype, int addr, bool vec, const StreamArgs& a, hipStream_t s);
-hipError_t launch_fill_normal(int dtype, void* w, int64_t n, uint64_t seed, uint32_t domain, float stddev, bool vec,
+hipError_t launch_perturb(int dtype, int aux, int addr, const StreamArgs& a, hipStream_t s);
+hipError_t launch_restore_copy(int dtype, int addr, const StreamArgs& a, hipStream_t s);
+hipError_t launch_restore_master(int addr, const StreamArgs& a, hipStream_t s);
+hipError_t launch_backup_copy(int dtype, int addr, const StreamArgs& a, hipStream_t s);
+hipError_t launch_fill_normal(int dtype, void* w, int64_t n, uint64_t seed, uint32_t domain, float stddev,
                               hipStream_t s);
-hipError_t launch_stage_master(int dtype, int addr, bool vec, const StreamArgs& a, hipStream_t s);
-hipError_t launch_update(int dtype, bool master, int addr, bool vec, const UpdateArgs& a, hipStream_t s);
+hipError_t launch_stage_master(int dtype, int addr, const StreamArgs& a, hipStream_t s);
+hipError_t launch_update(int dtype, bool master, int addr, const UpdateArgs& a, hipStream_t s);
 hipError_t launch_update_step(int dtype, int addr, const StepArgs& a, hipStream_t s);
 hipError_t launch_normalize(const NormalizeArgs& a, hipStream_t s);
 hipError_t launch_partition(const PartitionArgs& a, hipStream_t s);

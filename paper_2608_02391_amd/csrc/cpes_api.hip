@@ -297,6 +297,33 @@ int host_backup_copy(void* w_dev, int64_t numel, int dtype, const cpes_subspace*
     return hip_status(cpes::launch_restore_copy(dtype, addr_mode(s), a, st), fn);
 }
 
+// The stream of `seed` among streams [first, n_streams), appended if it is new.
+int32_t stream_number(cpes::MemberTable& t, int first, int& n_streams, uint64_t seed)
+{
+    const uint32_t lo = (uint32_t)seed, hi = (uint32_t)(seed >> 32);
+    for (int u = first; u < n_streams; ++u)
+        if (t.seed_lo[u] == lo && t.seed_hi[u] == hi) return u;
+    t.seed_lo[n_streams] = lo;
+    t.seed_hi[n_streams] = hi;
+    return n_streams++;
+}
+
+// The members of every stream, stream by stream, in member order within each.
+void list_members(cpes::MemberTable& t, int32_t n, int n_streams, const int32_t* stream_of, const int8_t* signs)
+{
+    uint16_t next[CPES_MAX_MEMBERS] = {0};
+    for (int32_t i = 0; i < n; ++i) ++next[stream_of[i]];
+    uint16_t at = 0;
+    for (int u = 0; u < n_streams; ++u) {
+        t.first_member[u] = at;
+        at = (uint16_t)(at + next[u]);
+        next[u] = t.first_member[u];
+    }
+    t.first_member[n_streams] = at;
+    for (int32_t i = 0; i < n; ++i)
+        t.member[next[stream_of[i]]++] = (uint16_t)(i | (signs[i] < 0 ? cpes::kNegative : 0));
+}
+
 }  // namespace
 
 extern "C" {
@@ -583,19 +610,13 @@ int cpes_update(void* w_dev, int64_t numel, int dtype, const cpes_subspace* s, f
         return fail(CPES_ERR_INVALID_ARGUMENT, "%s: a master copy needs bf16 weights", fn);
     cpes::UpdateArgs a;
     std::memset(&a, 0, sizeof a);
+    int32_t stream_of[CPES_MAX_MEMBERS];
     int n_streams = 0;
     for (int32_t i = 0; i < n; ++i) {
         if ((rc = check_sign(signs_host[i], fn))) return rc;
-        int u = 0;
-        while (u < n_streams && ((uint64_t)a.seed_lo[u] | ((uint64_t)a.seed_hi[u] << 32)) != seeds_host[i]) ++u;
-        if (u == n_streams) {
-            a.seed_lo[u] = (uint32_t)seeds_host[i];
-            a.seed_hi[u] = (uint32_t)(seeds_host[i] >> 32);
-            ++n_streams;
-        }
-        a.member_stream[i] = (uint8_t)u;
-        a.member_sign[i] = signs_host[i];
+        stream_of[i] = stream_number(a.members, 0, n_streams, seeds_host[i]);
     }
+    list_members(a.members, n, n_streams, stream_of, signs_host);
     if (s->length == 0) return CPES_OK;
     const double step = scale_mode == CPES_SCALE_ALPHA_OVER_N_SIGMA ? (double)alpha / ((double)n * (double)sigma)
                                                                     : (double)alpha / (double)n;
@@ -663,21 +684,13 @@ int update_step_impl(void* w_dev, int64_t numel, int dtype, int32_t K, const int
     cpes::StepArgs a;
     std::memset(&a, 0, sizeof a);
     // streams: distinct (subspace, seed) pairs, grouped by subspace, in order of first appearance
+    int32_t stream_of[CPES_MAX_MEMBERS];
     int n_streams = 0;
     for (int32_t k = 0; k < K; ++k) {
         a.stream_begin[k] = n_streams;
-        for (int32_t i = 0; i < n; ++i) {
-            if (subspace_host[i] != k) continue;
-            int u = a.stream_begin[k];
-            while (u < n_streams && ((uint64_t)a.seed_lo[u] | ((uint64_t)a.seed_hi[u] << 32)) != seeds_host[i]) ++u;
-            if (u == n_streams) {
-                a.seed_lo[u] = (uint32_t)seeds_host[i];
-                a.seed_hi[u] = (uint32_t)(seeds_host[i] >> 32);
-                ++n_streams;
-            }
-            a.member_stream[i] = (uint8_t)u;
-            a.member_sign[i] = signs_host[i];
-        }
+        for (int32_t i = 0; i < n; ++i)
+            if (subspace_host[i] == k)
+                stream_of[i] = stream_number(a.members, a.stream_begin[k], n_streams, seeds_host[i]);
         if (count[k] > 0) {
             const float sig = sigma_host[k];
             if (scale_mode == CPES_SCALE_ALPHA_OVER_N_SIGMA && (!std::isfinite(sig) || sig <= 0.0f))
@@ -689,6 +702,7 @@ int update_step_impl(void* w_dev, int64_t numel, int dtype, int32_t K, const int
         }
     }
     a.stream_begin[K] = n_streams;
+    list_members(a.members, n, n_streams, stream_of, signs_host);
     const int N = dtype == CPES_BF16 ? 8 : 4;
     int64_t tiles = 0;
     for (int32_t k = 0; k <= K; ++k) {

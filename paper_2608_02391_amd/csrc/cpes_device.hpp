@@ -35,11 +35,15 @@ __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c)
     return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
 }
 
-__device__ __forceinline__ Words4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
-                                                uint32_t k0, uint32_t k1)
+// The rounds from `first` on, keys as at round 0.
+template <int FIRST>
+__device__ __forceinline__ Words4 philox_rounds(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0,
+                                                uint32_t k1)
 {
+    k0 += FIRST * kWeylA;
+    k1 += FIRST * kWeylB;
 #pragma unroll
-    for (int r = 0; r < 10; ++r) {
+    for (int r = FIRST; r < 10; ++r) {
         const uint64_t pa = (uint64_t)kPhiloxMulA * c0;
         const uint64_t pb = (uint64_t)kPhiloxMulB * c2;
         const uint32_t n0 = xor3((uint32_t)(pb >> 32), c1, k0);
@@ -54,10 +58,32 @@ __device__ __forceinline__ Words4 philox4x32_10(uint32_t c0, uint32_t c1, uint32
     return Words4{c0, c1, c2, c3};
 }
 
-// Block q of stream (key, domain): counter (lo32 q, hi32 q, domain, 0).
-__device__ __forceinline__ Words4 stream_block(uint32_t k0, uint32_t k1, uint32_t domain, uint64_t q)
+__device__ __forceinline__ Words4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
+                                                uint32_t k0, uint32_t k1)
 {
-    return philox4x32_10((uint32_t)q, (uint32_t)(q >> 32), domain, 0u, k0, k1);
+    return philox_rounds<0>(c0, c1, c2, c3, k0, k1);
+}
+
+// Block q of stream (key, domain): counter (lo32 q, hi32 q, domain, 0).  Q is
+// uint32_t where every block of a launch is known to be below 2^32 (noise
+// indices below 2^34).  With three counter words the same in all lanes, half
+// of the first two rounds then belongs to the scalar unit: they are written
+// out with plain xors, which the compiler can take there (xor3 is opaque).
+// VALU instructions per 8 normals in the loops of the update and of the
+// in-place perturbation, with the constants held below: 242 and 260, against
+// 249 and 270.
+template <typename Q>
+__device__ __forceinline__ Words4 stream_block(uint32_t k0, uint32_t k1, uint32_t domain, Q q)
+{
+    if constexpr (sizeof(Q) == 8) {
+        return philox4x32_10((uint32_t)q, (uint32_t)(q >> 32), domain, 0u, k0, k1);
+    } else {
+        const uint64_t pa = (uint64_t)kPhiloxMulA * q, pb = (uint64_t)kPhiloxMulB * domain;
+        const uint32_t c0 = (uint32_t)(pb >> 32) ^ k0, c2 = (uint32_t)(pa >> 32) ^ k1;
+        const uint64_t qa = (uint64_t)kPhiloxMulA * c0, qb = (uint64_t)kPhiloxMulB * c2;
+        return philox_rounds<2>((uint32_t)(qb >> 32) ^ ((uint32_t)pb ^ (k0 + kWeylA)), (uint32_t)qb,
+                                (uint32_t)pa ^ ((uint32_t)(qa >> 32) ^ (k1 + kWeylB)), (uint32_t)qa, k0, k1);
+    }
 }
 
 // ------------------------------------------------------------ Box-Muller --
@@ -76,12 +102,21 @@ __device__ __forceinline__ Words4 stream_block(uint32_t k0, uint32_t k1, uint32_
 static_assert(sizeof(LogEntry) == 16 && sizeof(AngleEntry) == 16, "16-byte table entries");
 static_assert(sizeof(BmTables) == 16 * (kLogTableSize + kAngleTableSize), "tables are packed 16-byte entries");
 
+// The tables in LDS, and two polynomial constants in vector registers: an
+// instruction reads one constant from the scalar registers, so an fma of two
+// constants needs the other one in a vector register, where the compiler would
+// move it again in every round of a loop.
+struct Bm {
+    const BmTables* t;
+    double ang_a3, ang_b2;
+};
+
 // Copy both tables into LDS; every thread of the workgroup must call it (it
 // ends with a barrier).  With a BLOCK-thread workgroup each thread issues all
 // of its 16-byte loads before the first LDS store, so the workgroup waits for
 // one memory round trip instead of one per entry it copies.
 template <int BLOCK>
-__device__ __forceinline__ const BmTables* stage_bm_tables()
+__device__ __forceinline__ Bm stage_bm_tables()
 {
     constexpr int kWords = (int)(sizeof(BmTables) / sizeof(uint4));
     constexpr int kPer = (kWords + BLOCK - 1) / BLOCK;
@@ -100,7 +135,9 @@ __device__ __forceinline__ const BmTables* stage_bm_tables()
         for (int i = threadIdx.x; i < kWords; i += blockDim.x) dst[i] = src[i];
     }
     __syncthreads();
-    return &tb;
+    Bm bm = {&tb, kAngA3, kAngB2};
+    asm volatile("" : "+v"(bm.ang_a3), "+v"(bm.ang_b2));
+    return bm;
 }
 
 template <typename E>
@@ -118,13 +155,14 @@ __device__ __forceinline__ E lds_entry(const E* table, uint32_t byte_off)
 // with -2 ln(1 + r) = r q(r), q of degree 4 (Taylor).  Relative error at
 // most 2^-46.5 over all 2^24 inputs.  B_0 carries 2^-400 in place of 0, so
 // U = 1 gives L = 2^-400 (a zero normal after rounding) and L is never 0.
-__device__ __forceinline__ double bm_log_term(uint32_t a, const BmTables* tb)
+__device__ __forceinline__ double bm_log_term(uint32_t a, const Bm& tb)
 {
-    const uint32_t m7 = ((a >> 8) + 1u) << 7;             // m 2^7 <= 2^31
+    uint32_t m7;                                           // m 2^7 = (a >> 8) 2^7 + 2^7 <= 2^31
+    asm("v_lshl_add_u32 %0, %1, 7, %2" : "=v"(m7) : "v"(a >> 8), "s"(128u));
     const uint32_t e = (uint32_t)__builtin_clz(m7);        // lz - 7, in [0, 24]
     const uint32_t mn = m7 << e;
     const uint32_t byte_off = (mn >> (27 - kLogTableBits)) & ((kLogTableSize - 1) << 4);   // entry * 16
-    const LogEntry t = lds_entry(tb->log, byte_off);
+    const LogEntry t = lds_entry(tb.t->log, byte_off);
     const double r = __builtin_fma((double)mn, t.inv, -1.0);
     const double base = __builtin_fma((double)e, kTwoLn2, t.b);
     double q = -0x1.999999999999ap-2;                      // -2/5
@@ -145,7 +183,7 @@ __device__ __forceinline__ double bm_sqrt(double L)
     return __builtin_fma(g, __builtin_fma(-g, h, 0.5), g);
 }
 
-__device__ __forceinline__ double bm_radius(uint32_t a, const BmTables* tb)
+__device__ __forceinline__ double bm_radius(uint32_t a, const Bm& tb)
 {
     return bm_sqrt(bm_log_term(a, tb));
 }
@@ -159,7 +197,7 @@ __device__ __forceinline__ double bm_radius(uint32_t a, const BmTables* tb)
 // reduces to +-sin delta and keeps its relative accuracy; the table's signed
 // zeros make the quarter-turn angles come out as in an exact quadrant
 // reduction.  Relative error below 2^-50 over all 2^24 inputs.
-__device__ __forceinline__ void bm_angle(uint32_t b, const BmTables* tb, double& cos_t, double& sin_t)
+__device__ __forceinline__ void bm_angle(uint32_t b, const Bm& tb, double& cos_t, double& sin_t)
 {
     // Adding 0x100 to b cannot carry out of its low byte, so bits 8..31 of
     // b + 0x100 are m mod 2^24 (m = 2^24 wraps to 0, the same angle); x is
@@ -168,17 +206,17 @@ __device__ __forceinline__ void bm_angle(uint32_t b, const BmTables* tb, double&
     const uint32_t s8 = b + 0x100u;
     const double x = (double)((int32_t)(s8 << 9) >> 17);
     const uint32_t byte_off = ((b + 0x400100u) >> (31 - kAngleTableBits - 3)) & ((kAngleTableSize - 1) << 4);
-    const AngleEntry t = lds_entry(tb->angle, byte_off);
+    const AngleEntry t = lds_entry(tb.t->angle, byte_off);
     const double x2 = x * x;                               // exact
-    const double sd = x * __builtin_fma(x2, __builtin_fma(x2, kAngA5, kAngA3), kAngA1);
-    const double cd = __builtin_fma(x2, __builtin_fma(x2, kAngB4, kAngB2), 1.0);
+    const double sd = x * __builtin_fma(x2, __builtin_fma(x2, kAngA5, tb.ang_a3), kAngA1);
+    const double cd = __builtin_fma(x2, __builtin_fma(x2, kAngB4, tb.ang_b2), 1.0);
     cos_t = __builtin_fma(t.c, cd, -(t.s * sd));
     sin_t = __builtin_fma(t.s, cd, t.c * sd);
 }
 
 // Two normals of the pair (a, b): z_even = fp32(rho cos theta), z_odd =
 // fp32(rho sin theta).
-__device__ __forceinline__ void bm_pair(uint32_t a, uint32_t b, const BmTables* tb, float& z_even, float& z_odd)
+__device__ __forceinline__ void bm_pair(uint32_t a, uint32_t b, const Bm& tb, float& z_even, float& z_odd)
 {
     const double rho = bm_radius(a, tb);
     double c, s;
@@ -188,7 +226,8 @@ __device__ __forceinline__ void bm_pair(uint32_t a, uint32_t b, const BmTables* 
 }
 
 // Four normals of block q: positions 4q .. 4q+3 (domain 0 is the noise).
-__device__ __forceinline__ void normals4(uint32_t k0, uint32_t k1, uint64_t q, const BmTables* tb, float z[4],
+template <typename Q>
+__device__ __forceinline__ void normals4(uint32_t k0, uint32_t k1, Q q, const Bm& tb, float z[4],
                                          uint32_t domain = 0u)
 {
     const Words4 x = stream_block(k0, k1, domain, q);
@@ -197,11 +236,12 @@ __device__ __forceinline__ void normals4(uint32_t k0, uint32_t k1, uint64_t q, c
 }
 
 // Eight normals of blocks q and q+1: positions 4q .. 4q+7.
-__device__ __forceinline__ void normals8(uint32_t k0, uint32_t k1, uint64_t q, const BmTables* tb, float z[8],
+template <typename Q>
+__device__ __forceinline__ void normals8(uint32_t k0, uint32_t k1, Q q, const Bm& tb, float z[8],
                                          uint32_t domain = 0u)
 {
     const Words4 x = stream_block(k0, k1, domain, q);
-    const Words4 y = stream_block(k0, k1, domain, q + 1u);
+    const Words4 y = stream_block(k0, k1, domain, (Q)(q + 1u));
     bm_pair(x.x, x.y, tb, z[0], z[1]);
     bm_pair(x.z, x.w, tb, z[2], z[3]);
     bm_pair(y.x, y.y, tb, z[4], z[5]);

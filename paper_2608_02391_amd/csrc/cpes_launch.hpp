@@ -9,9 +9,9 @@ namespace cpes {
 
 constexpr int kBlock = 256;             // threads per workgroup for streaming kernels
 constexpr int64_t kMaxGrid = 1 << 20;   // workgroups per launch; larger jobs loop
-// Workgroups per launch of the noise kernels on contiguous and chunked
-// subspaces, which stage the 12 KiB Box-Muller tables (sizeof(BmTables)) in
-// LDS per workgroup: a few per CU, each looping over many units.
+// Workgroups per launch of the noise kernels, which stage the 12 KiB
+// Box-Muller tables (sizeof(BmTables)) in LDS per workgroup, up to which a
+// thread takes one unit; see noise_grid_cap for larger launches.
 constexpr int64_t kRngMaxGrid = 8192;
 
 // Subspace addressing modes (see cpes_subspace).  kAddrGather32 reads a
@@ -37,8 +37,17 @@ struct StreamArgs {
 enum AuxKind { kAuxNone = 0, kAuxSnapshot = 1, kAuxMaster = 2, kAuxBackup = 3 };
 
 // Update: up to kMaxMembers members folded into up to kMaxMembers distinct
-// noise streams; all of it travels in the kernel argument block.
+// noise streams; all of it travels in the kernel argument block.  Members are
+// listed stream by stream, in member order within a stream.
 constexpr int kMaxMembers = 256;
+
+struct MemberTable {
+    uint32_t seed_lo[kMaxMembers];              // of each stream
+    uint32_t seed_hi[kMaxMembers];
+    uint16_t first_member[kMaxMembers + 1];     // first entry of member[] of each stream
+    uint16_t member[kMaxMembers];               // member index | kNegative for sign -1
+};
+constexpr uint16_t kNegative = 0x8000;
 
 struct UpdateArgs {
     void* w;
@@ -53,10 +62,7 @@ struct UpdateArgs {
     int32_t n_streams;
     int32_t chunk_shift;
     int64_t noise0;         // noise index of position 0
-    uint32_t seed_lo[kMaxMembers];
-    uint32_t seed_hi[kMaxMembers];
-    uint8_t member_stream[kMaxMembers];
-    int8_t member_sign[kMaxMembers];
+    MemberTable members;
 };
 
 // Whole-step update: every subspace of a partition with its own members, one
@@ -78,10 +84,7 @@ struct StepArgs {
     int64_t tile_begin[kMaxStepSubspaces + 1];     // first wave tile of subspace k
     int32_t stream_begin[kMaxStepSubspaces + 1];   // streams of subspace k
     float step[kMaxStepSubspaces];
-    uint32_t seed_lo[kMaxMembers];
-    uint32_t seed_hi[kMaxMembers];
-    uint8_t member_stream[kMaxMembers];
-    int8_t member_sign[kMaxMembers];
+    MemberTable members;
 };
 
 struct NormalizeArgs {

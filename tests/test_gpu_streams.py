@@ -1,0 +1,167 @@
+"""The branches of the noise and copy kernels that neither length nor layout
+selects: streams whose coefficient is zero, noise blocks above 2^32, and
+ranges and side buffers that start at no vector boundary."""
+import numpy as np
+import pytest
+
+import paper_2608_02391_amd as cp
+import synthetic as S
+from tests.gpu_helpers import describe_mismatch, f32_close, to_dev, to_host, torch, ulp_bf16, ulp_f32
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def T():
+    t = torch()
+    assert t.cuda.is_available(), "GPU tests need an MI355X"
+    cp.load()
+    return t
+
+
+def _members(n, zero):
+    """n members with rewards, those in `zero` with a coefficient of exactly
+    zero: a reward of 0 or -0, or a mirrored pair with equal rewards."""
+    rng = np.random.default_rng(n)
+    seeds, signs, r = list(range(50, 50 + n)), [1] * n, rng.normal(size=n).astype(np.float32)
+    for i in zero:
+        r[i] = -0.0 if i % 2 else 0.0
+    if n >= 6:                                            # members 2 and 3 cancel
+        seeds[3], signs[3] = seeds[2], -1
+        r[3] = r[2]
+    return seeds, signs, r
+
+
+@pytest.mark.parametrize("n,zero", [
+    (1, []), (1, [0]), (5, [0, 4]), (6, [0, 5]), (64, [0, 62, 63]), (65, [64]), (66, list(range(66))),
+    (130, list(range(60, 70)) + [127, 128, 129]), (256, list(range(0, 256, 3)) + [63, 64, 191, 192, 255])])
+@pytest.mark.parametrize("kind", ["contiguous", "map"])
+def test_streams_with_zero_coefficients(orc, T, n, zero, kind):
+    """An update whose members partly cancel equals the oracle's; one whose
+    members all do leaves the weights' bits alone."""
+    length = 2 * 512 + 77
+    w = S.host_weights(4 * length, S.F32, n)
+    index = np.sort(np.random.default_rng(1).permutation(4 * length)[:length]).astype(np.int64) if kind == "map" else None
+    dmap = to_dev(index) if kind == "map" else None
+    seeds, signs, r = _members(n, zero)
+    dw = to_dev(w)
+    sub = cp.subspace(0 if kind == "map" else 5, length, dmap)
+    cp.cpes_update(dw, sub, seeds, signs, to_dev(r), 0.01, 1.0, cp.SCALE_ALPHA_OVER_N)
+    ref = w.copy()
+    orc.update(ref, 0 if kind == "map" else 5, length, seeds, signs, r, np.float32(0.01), np.float32(1.0),
+               S.SCALE_ALPHA_OVER_N, index=index)
+    T.cuda.synchronize()
+    got = to_host(dw)
+    # the bar of updated fp32 weights
+    assert f32_close(got, ref), describe_mismatch(got, ref)
+    if len(zero) == n:
+        assert np.array_equal(got, w)
+
+
+def test_step_ranges_cross_the_words_of_the_stream_bits(orc, T):
+    """The whole-step update: subspaces whose streams begin inside a 64-bit
+    word, end at one, or are all zero, one without members."""
+    counts = [63, 2, 0, 64, 65, 1, 61]                    # 256 members
+    K, n = len(counts), sum(counts)
+    ks = np.repeat(np.arange(K), counts)
+    rng = np.random.default_rng(3)
+    r = rng.normal(size=n).astype(np.float32)
+    r[rng.permutation(n)[:120]] = 0.0
+    r[ks == 5] = 0.0                                       # a subspace none of whose streams contributes
+    order = rng.permutation(n)
+    ks, r = ks[order], r[order]
+    seeds, signs = list(range(900, 900 + n)), [1 - 2 * (i % 2) for i in range(n)]
+    bounds = [0, 1000, 1777, 2000, 4099, 5000, 6001, 7003]
+    w = S.host_weights(7003, S.F32, 8)
+    sigmas = [1.0] * K
+    dw = to_dev(w)
+    cp.cpes_update_step(dw, bounds, seeds, signs, ks.tolist(), to_dev(r), 0.01, sigmas, cp.SCALE_ALPHA_OVER_N)
+    ref = w.copy()
+    orc.update_step(ref, bounds, seeds, signs, ks, r, np.float32(0.01), sigmas, S.SCALE_ALPHA_OVER_N)
+    T.cuda.synchronize()
+    got = to_host(dw)
+    assert f32_close(got, ref), describe_mismatch(got, ref)
+    assert np.array_equal(got[5000:6001], w[5000:6001]) and np.array_equal(got[1777:2000], w[1777:2000])
+
+
+@pytest.mark.parametrize("noise0", [(1 << 34) - 4096, (1 << 34) - 1024, 1 << 34, (1 << 36) + 8])
+@pytest.mark.parametrize("dtype", [S.BF16, S.F32])
+@pytest.mark.parametrize("layout", ["contiguous", "map", "map_ascending"])
+def test_noise_blocks_around_2_to_32(orc, T, noise0, dtype, layout):
+    """A shard whose noise blocks lie below, across or above 2^32 (the kernels
+    for short blocks end there)."""
+    length = 4096
+    w = S.host_weights(2 * length, dtype, 4)
+    index = np.arange(0, 2 * length, 2, dtype=np.int64) if layout != "contiguous" else None
+    sub = cp.subspace(0, length, None if index is None else to_dev(index), noise_offset=noise0,
+                      ascending=layout == "map_ascending")
+    dw, ref = to_dev(w), w.copy()
+    cp.cpes_perturb(dw, sub, 0.25, 77, -1)
+    orc.perturb(ref, 0, length, np.float32(0.25), 77, -1, index=index, j0=noise0)
+    T.cuda.synchronize()
+    got = to_host(dw)
+    assert (ulp_bf16(got, ref) if dtype == S.BF16 else ulp_f32(got, ref)).max() <= 1      # the bar of perturbations
+    if dtype == S.F32:
+        r = np.array([0.5, -1.25, 0.0], dtype=np.float32)
+        dw, ref = to_dev(w), w.copy()
+        cp.cpes_update(dw, sub, [1, 2, 3], [1, -1, 1], to_dev(r), 0.01, 1.0, cp.SCALE_ALPHA_OVER_N)
+        orc.update(ref, 0, length, [1, 2, 3], [1, -1, 1], r, np.float32(0.01), np.float32(1.0), S.SCALE_ALPHA_OVER_N,
+                   index=index, j0=noise0)
+        T.cuda.synchronize()
+        assert f32_close(to_host(dw), ref)
+
+
+@pytest.mark.parametrize("length", [1, 7, 8, 9, 2047, 2048, 2049, 70001])
+@pytest.mark.parametrize("dtype", [S.BF16, S.F32])
+@pytest.mark.parametrize("layout", ["contiguous", "chunk", "map"])
+def test_any_element_alignment(orc, T, length, dtype, layout):
+    """Weights, backup and master each at their own element offset from a
+    vector boundary: the same bits as from aligned copies."""
+    C = 256
+    numel = 4 * length + 8 * C
+    base = S.host_weights(numel + 8, dtype, length)
+    if layout == "contiguous":
+        make = lambda off: cp.subspace(off, length)
+    elif layout == "chunk":
+        chunks = to_dev(np.random.default_rng(2).permutation(numel // C)[:length // C + 1].astype(np.int64))
+        make = lambda off: cp.subspace(0, length, chunks, C)
+    else:
+        index = to_dev(np.sort(np.random.default_rng(2).permutation(numel)[:length + 3]).astype(np.int64))
+        make = lambda off: cp.subspace(3, length, index)
+    tdt = T.bfloat16 if dtype == S.BF16 else T.float32
+    r = to_dev(np.array([0.5, -1.0], dtype=np.float32))
+
+    def passes(shift, side):
+        """Weights `shift` elements past a vector boundary, side buffers `side`."""
+        buf = T.zeros(numel + 16, dtype=tdt, device="cuda")
+        w = buf[shift:shift + numel]
+        w.copy_(to_dev(base)[:numel])
+        sub = make(16)
+        bak = T.zeros(length + 8, dtype=tdt, device="cuda")[side:side + length]
+        out = []
+        cp.cpes_perturb(w, sub, 0.5, 3, 1, aux=bak, aux_mode=cp.AUX_SNAPSHOT)
+        out += [w.clone(), bak.clone()]
+        cp.cpes_perturb(w, sub, 0.5, 4, 1)
+        cp.cpes_perturb(w, sub, 0.25, 5, -1, aux=bak, aux_mode=cp.AUX_BACKUP)
+        out.append(w.clone())
+        cp.cpes_restore(w, sub, aux=bak)
+        out.append(w.clone())
+        cp.cpes_backup(w, sub, bak)
+        master = T.zeros(length + 8, dtype=T.float32, device="cuda")[side:side + length]
+        cp.cpes_stage_master(w, sub, master)
+        cp.cpes_update(w, sub, [8, 9], [1, 1], r, 0.01, 1.0, master=master if dtype == S.BF16 else None)
+        out += [w.clone(), bak.clone(), master.clone()]
+        if dtype == S.BF16:
+            cp.cpes_perturb(w, sub, 0.5, 6, 1, aux=master, aux_mode=cp.AUX_MASTER)
+            out.append(w.clone())
+            cp.cpes_restore(w, sub, aux=master, aux_mode=cp.AUX_MASTER)
+        cp.cpes_update_step(w, [16, 16 + min(length, 77), 16 + length], [8, 9], [1, 1], [0, 1], r, 0.01, [1.0, 1.0])
+        out.append(w.clone())
+        assert not bool(buf[:shift].any()) and not bool(buf[shift + numel:].any())        # nothing outside
+        return out
+
+    want = passes(0, 0)
+    assert not bool(T.equal(want[0], want[3]))
+    for shift, side in ((1, 0), (0, 1), (3, 5), (7, 2)):
+        for a, b in zip(want, passes(shift, side)):
+            assert T.equal(a, b)

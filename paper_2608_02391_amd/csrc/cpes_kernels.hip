@@ -1190,24 +1190,25 @@ __global__ __launch_bounds__(kBlock) void k_update_step(StepArgs a)
 }
 
 // -------------------------------------------------------------- normalise --
-// One workgroup.  The rewards are sorted in LDS by the 64-bit key
-// (group, value, index) -- the value as an order-preserving 32-bit image of
-// the fp32 bits, -0 taken as +0 -- with a bitonic network.  Each group is
-// then one run of the sorted keys, in a canonical order (ascending value).
-// Z: one wave per group sums the run in fp64 (lane l takes run entries
-// l, l + 64, ... in order, then an xor-shuffle butterfly combines the 64
-// partial sums; every lane ends with the same total), for the mean and then
-// for the squared deviations.  RANK: the rank of an entry is the start of
-// its run of equal values within its group, the number of ties the run's
-// length, both found by binary search.
-constexpr int kNormThreads = 1024;
+// Bound by latency: at most 4,096 rewards, 16 KiB.  Three kernels share the
+// work by what has to be known of the other rewards:
+//  * k_normalize_z, joint z-scores: one workgroup holds all rewards in
+//    registers and needs two sums;
+//  * k_normalize_z_groups: a workgroup per group, which reads all rewards and
+//    sums its own;
+//  * k_normalize_rank: a workgroup per 16 rewards, which counts, for each of
+//    them, the smaller and the equal ones among all;
+// and k_normalize (sorted, one workgroup) takes the last two where the output
+// overlaps the inputs, since there another workgroup's result could be read
+// for a reward.  Per call, launch included, of 4,096 rewards: joint z-scores
+// 75 -> 5.2 us, ranks 64 -> 8.8 us, z-scores in 64 groups 63 -> 7.8 us (first
+// figure: sorted); of 30 rewards 5.6 -> 5.1 us.
+//
+// The fp64 sums are taken in a fixed order (a thread's entries in index order,
+// an xor-shuffle butterfly over the wave, the waves in order), so results are
+// the same from run to run.
 constexpr int kNormMaxN = 4096;
 constexpr int kNormMaxGroups = 1024;
-constexpr int kNormIdxBits = 12;                 // index < kNormMaxN
-constexpr int kNormValShift = kNormIdxBits;      // value bits 12 .. 43
-constexpr int kNormGroupShift = kNormIdxBits + 32;   // group bits 44 .. 53
-static_assert((1 << kNormIdxBits) >= kNormMaxN && kNormMaxGroups <= (1 << (64 - kNormGroupShift - 1)),
-              "index, value and group fit the sort key");
 
 __device__ __forceinline__ uint32_t order_bits(float v)
 {
@@ -1218,6 +1219,193 @@ __device__ __forceinline__ float from_order_bits(uint32_t o)
 {
     return __uint_as_float((o & 0x80000000u) ? (o & 0x7FFFFFFFu) : ~o);
 }
+
+__device__ __forceinline__ double wave_sum(double x)
+{
+#pragma unroll
+    for (int m = 32; m > 0; m >>= 1) x += __shfl_xor(x, m, 64);
+    return x;
+}
+
+// Sum over the workgroup, the same in every thread; `part` is written once per call.
+template <int WAVES>
+__device__ __forceinline__ double block_sum(double x, double* part)
+{
+    x = wave_sum(x);
+    if (WAVES == 1) return x;
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x / 64] = x;
+    __syncthreads();
+    double s = 0.0;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) s += part[w];
+    return s;
+}
+
+// Whether `x` is set in any thread of the workgroup.
+template <int WAVES>
+__device__ __forceinline__ int block_or(int x, int* part)
+{
+    const int any = (__builtin_amdgcn_ballot_w64(x & 1) != 0 ? 1 : 0) | (__builtin_amdgcn_ballot_w64(x & 2) != 0 ? 2 : 0);
+    if (WAVES == 1) return any;
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x / 64] = any;
+    __syncthreads();
+    int s = 0;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) s |= part[w];
+    return s;
+}
+
+// Joint z-scores, four rewards per thread: one wave up to 256 rewards (no
+// barrier), 4 and 16 waves above.
+template <int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void k_normalize_z(NormalizeArgs a)
+{
+#pragma clang fp contract(off)
+    constexpr int kPer = 4;
+    __shared__ double part[2][WAVES];
+    __shared__ int flag[WAVES];
+    float r[kPer];
+    int bad = 0;
+    double sum = 0.0;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const int i = (int)threadIdx.x + 64 * WAVES * k;
+        r[k] = i < a.n ? a.r[i] : 0.0f;
+        if (!__builtin_isfinite(r[k])) bad = 1;
+        sum += (double)r[k];
+    }
+    bad = block_or<WAVES>(bad, flag);
+    const double mu = block_sum<WAVES>(sum, part[0]) / (double)a.n;
+    double dev2 = 0.0;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const double dev = (int)threadIdx.x + 64 * WAVES * k < a.n ? (double)r[k] - mu : 0.0;
+        dev2 += dev * dev;
+    }
+    const double sd = __builtin_sqrt(block_sum<WAVES>(dev2, part[1]) / (double)a.n);
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const int i = (int)threadIdx.x + 64 * WAVES * k;
+        if (i < a.n) a.out[i] = bad == 0 && sd > 0.0 ? (float)(((double)r[k] - mu) / sd) : 0.0f;
+    }
+    if (a.status && threadIdx.x == 0) *a.status = bad;
+}
+
+// Failures of a grouped or ranked call: every output 0, written by the first
+// workgroup alone.  Returns whether the call failed.
+__device__ __forceinline__ bool normalize_failed(const NormalizeArgs& a, int bad)
+{
+    const int status = (bad & 2) ? 2 : (bad & 1);
+    if (blockIdx.x == 0) {
+        if (status != 0)
+            for (int i = threadIdx.x; i < a.n; i += blockDim.x) a.out[i] = 0.0f;
+        if (a.status && threadIdx.x == 0) *a.status = status;
+    }
+    return status != 0;
+}
+
+// Z-scores by group: workgroup g sums the rewards of group g.
+__global__ __launch_bounds__(kBlock) void k_normalize_z_groups(NormalizeArgs a)
+{
+#pragma clang fp contract(off)
+    constexpr int kWaves = kBlock / 64, kPer = kNormMaxN / kBlock;
+    __shared__ double part[3][kWaves];
+    __shared__ int flag[kWaves];
+    float r[kPer];
+    uint32_t mine = 0;
+    int bad = 0;
+    double sum = 0.0;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const int i = (int)threadIdx.x + kBlock * k;
+        const int32_t g = i < a.n ? a.group[i] : 0;
+        r[k] = i < a.n ? a.r[i] : 0.0f;
+        if (!__builtin_isfinite(r[k])) bad |= 1;
+        if (g < 0 || g >= a.n_groups) bad |= 2;
+        if (i < a.n && g == (int32_t)blockIdx.x) {
+            mine |= 1u << k;
+            sum += (double)r[k];
+        }
+    }
+    if (normalize_failed(a, block_or<kWaves>(bad, flag))) return;
+    const double c = block_sum<kWaves>((double)__builtin_popcount(mine), part[0]);
+    const double mu = block_sum<kWaves>(sum, part[1]) / c;
+    double dev2 = 0.0;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const double dev = (mine >> k) & 1u ? (double)r[k] - mu : 0.0;
+        dev2 += dev * dev;
+    }
+    const double sd = __builtin_sqrt(block_sum<kWaves>(dev2, part[2]) / c);
+#pragma unroll
+    for (int k = 0; k < kPer; ++k)
+        if ((mine >> k) & 1u)
+            a.out[threadIdx.x + kBlock * k] = sd > 0.0 ? (float)(((double)r[k] - mu) / sd) : 0.0f;
+}
+
+// Centred ranks: 16 rewards per workgroup, 16 threads count for each of them,
+// every sixteenth entry of all rewards in LDS.
+constexpr int kRankPer = 16;
+
+template <bool GROUPS>
+__global__ __launch_bounds__(kBlock) void k_normalize_rank(NormalizeArgs a)
+{
+#pragma clang fp contract(off)
+    constexpr int kWaves = kBlock / 64, kThreads = kBlock / kRankPer;
+    __shared__ uint32_t value[kNormMaxN];
+    __shared__ uint16_t group[GROUPS ? kNormMaxN : 1];
+    __shared__ int flag[kWaves];
+    int bad = 0;
+    for (int i = threadIdx.x; i < a.n; i += kBlock) {
+        const float r = a.r[i];
+        if (!__builtin_isfinite(r)) bad |= 1;
+        value[i] = order_bits(r);
+        if (GROUPS) {
+            const int32_t g = a.group[i];
+            if (g < 0 || g >= a.n_groups) bad |= 2;
+            group[i] = (uint16_t)g;
+        }
+    }
+    if (normalize_failed(a, block_or<kWaves>(bad, flag))) return;
+    const int i = (int)blockIdx.x * kRankPer + (int)threadIdx.x / kThreads;
+    const uint32_t v = i < a.n ? value[i] : 0u;
+    const uint32_t g = GROUPS && i < a.n ? group[i] : 0u;
+    int less = 0, equal = 0, count = 0;
+#pragma unroll 8
+    for (int j = threadIdx.x % kThreads; j < a.n; j += kThreads) {
+        const uint32_t vj = value[j];
+        const bool same = GROUPS ? group[j] == g : true;       // no branches: every read is in flight at once
+        less += (int)(same & (vj < v));
+        equal += (int)(same & (vj == v));
+        if (GROUPS) count += (int)same;
+    }
+#pragma unroll
+    for (int m = kThreads / 2; m > 0; m >>= 1) {
+        less += __shfl_xor(less, m, 64);
+        equal += __shfl_xor(equal, m, 64);
+        if (GROUPS) count += __shfl_xor(count, m, 64);
+    }
+    if (!GROUPS) count = a.n;
+    if (i < a.n && threadIdx.x % kThreads == 0) {
+        const double rank = (double)less + 0.5 * (double)(equal - 1);
+        a.out[i] = count > 1 ? (float)(rank / (double)(count - 1) - 0.5) : 0.0f;
+    }
+}
+
+// Groups and ranks in place, one workgroup.  The rewards are sorted in LDS by
+// the 64-bit key (group, value, index) -- the value as an order-preserving
+// 32-bit image of the fp32 bits, -0 taken as +0 -- with a bitonic network.
+// Each group is then one run of the sorted keys.  Z: one wave per group sums
+// the run in fp64 (lane l takes run entries l, l + 64, ... in order, then the
+// butterfly), for the mean and then for the squared deviations.  RANK: the
+// rank of an entry is the start of its run of equal values within its group,
+// the number of ties the run's length, both found by binary search.
+constexpr int kNormThreads = 1024;
+constexpr int kNormIdxBits = 12;                 // index < kNormMaxN
+constexpr int kNormValShift = kNormIdxBits;      // value bits 12 .. 43
+constexpr int kNormGroupShift = kNormIdxBits + 32;   // group bits 44 .. 53
+static_assert((1 << kNormIdxBits) >= kNormMaxN && kNormMaxGroups <= (1 << (64 - kNormGroupShift - 1)),
+              "index, value and group fit the sort key");
 
 // First position p in [0, n) with keys[p] >= x (keys ascending).
 __device__ __forceinline__ int lower_bound_u64(const uint64_t* keys, int n, uint64_t x)
@@ -1231,13 +1419,6 @@ __device__ __forceinline__ int lower_bound_u64(const uint64_t* keys, int n, uint
             hi = mid;
     }
     return lo;
-}
-
-__device__ __forceinline__ double wave_sum(double x)
-{
-#pragma unroll
-    for (int m = 32; m > 0; m >>= 1) x += __shfl_xor(x, m, 64);
-    return x;
 }
 
 __global__ __launch_bounds__(kNormThreads) void k_normalize(NormalizeArgs a)
@@ -2174,9 +2355,32 @@ hipError_t launch_fill_normal(int dtype, void* w, int64_t n, uint64_t seed, uint
     return hipGetLastError();
 }
 
+namespace {
+
+bool overlap(const void* a, const void* b, int n)      // of n 4-byte entries
+{
+    const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b, len = 4 * (uintptr_t)n;
+    return a && b && x < y + len && y < x + len;
+}
+
+}  // namespace
+
 hipError_t launch_normalize(const NormalizeArgs& a, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_normalize, dim3(1), dim3(kNormThreads), 0, s, a);
+    const dim3 rank_grid((unsigned)((a.n + kRankPer - 1) / kRankPer));
+    if (a.mode == 0 && !a.group) {
+        if (a.n <= 256) hipLaunchKernelGGL(k_normalize_z<1>, dim3(1), dim3(64), 0, s, a);
+        else if (a.n <= 1024) hipLaunchKernelGGL(k_normalize_z<4>, dim3(1), dim3(256), 0, s, a);
+        else hipLaunchKernelGGL(k_normalize_z<16>, dim3(1), dim3(1024), 0, s, a);
+    } else if (overlap(a.out, a.r, a.n) || overlap(a.out, a.group, a.n)) {
+        hipLaunchKernelGGL(k_normalize, dim3(1), dim3(kNormThreads), 0, s, a);
+    } else if (a.mode == 0) {
+        hipLaunchKernelGGL(k_normalize_z_groups, dim3((unsigned)a.n_groups), dim3(kBlock), 0, s, a);
+    } else if (a.group) {
+        hipLaunchKernelGGL(k_normalize_rank<true>, rank_grid, dim3(kBlock), 0, s, a);
+    } else {
+        hipLaunchKernelGGL(k_normalize_rank<false>, rank_grid, dim3(kBlock), 0, s, a);
+    }
     return hipGetLastError();
 }
 

@@ -330,7 +330,8 @@ CPES_API int cpes_normalize_rewards(const float* r_dev, int32_t n, int mode, con
  * the output of cpes_normalize_rewards).  Members sharing a seed (mirrored
  * pairs) share one noise vector, which is generated once with coefficient
  * sum(sign * rnorm).  Each weight is read once and written once; the weighted
- * noise sum is accumulated in fp32 in order of first appearance of each seed.
+ * noise sum is accumulated in fp64 in order of first appearance of each seed
+ * and rounded once to fp32.
  *   master_dev == NULL: w[p(j)] = cast(fmaf(step, acc_j, w[p(j)])).
  *   master_dev != NULL: master[j] = fmaf(step, acc_j, master[j]) and
  *                       w[p(j)] = cast(master[j]) (device float32[length]).
@@ -366,7 +367,7 @@ CPES_API int cpes_update(void* w_dev, int64_t numel, int dtype, const cpes_subsp
  *   Members of one subspace sharing a seed share one noise stream.
  * sigma_host (host, K): the effective sigma_k each subspace was perturbed with.
  * Subspaces without members are left unchanged.  Each weight is read and
- * written once; accumulation in fp32 as in cpes_update.
+ * written once; accumulation in fp64 as in cpes_update.
  * Errors: NULL pointers, K < 1, n < 1, a sign not +-1, a member's subspace
  *   outside [0, K), decreasing offsets, contiguous range beyond numel, alpha
  *   not finite, sigma_k <= 0 for a subspace with members under the

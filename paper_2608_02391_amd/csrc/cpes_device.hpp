@@ -69,9 +69,9 @@ __device__ __forceinline__ Words4 philox4x32_10(uint32_t c0, uint32_t c1, uint32
 // indices below 2^34).  With three counter words the same in all lanes, half
 // of the first two rounds then belongs to the scalar unit: they are written
 // out with plain xors, which the compiler can take there (xor3 is opaque).
-// VALU instructions per 8 normals in the loops of the update and of the
-// in-place perturbation, with the constants held below: 242 and 260, against
-// 249 and 270.
+// That and the constants held in Bm save 7 and 10 VALU instructions per 8
+// normals in the loops of the update and of the in-place perturbation, which
+// have 226 and 256 with them.
 template <typename Q>
 __device__ __forceinline__ Words4 stream_block(uint32_t k0, uint32_t k1, uint32_t domain, Q q)
 {
@@ -93,7 +93,8 @@ __device__ __forceinline__ Words4 stream_block(uint32_t k0, uint32_t k1, uint32_
 // error and their product is rounded once to fp32, so the result is the
 // correctly rounded normal unless the exact value lies within ~2^-46
 // relative of a midpoint between two fp32 numbers (and it is always within
-// one fp32 ulp of it).
+// one fp32 ulp of it).  The update, which only needs weighted sums of normals,
+// adds the fp64 products themselves.
 //
 // Two small tables do most of the work (cpes_bm_tables.hpp, generated by
 // gen_bm_tables.py): 256 log entries and 512 points of the unit circle,
@@ -102,7 +103,8 @@ __device__ __forceinline__ Words4 stream_block(uint32_t k0, uint32_t k1, uint32_
 static_assert(sizeof(LogEntry) == 16 && sizeof(AngleEntry) == 16, "16-byte table entries");
 static_assert(sizeof(BmTables) == 16 * (kLogTableSize + kAngleTableSize), "tables are packed 16-byte entries");
 
-// The tables in LDS, and two polynomial constants in vector registers: an
+// The tables in LDS, the circle's points at half their size (bm_radius2 gives
+// twice the radius), and two polynomial constants in vector registers: an
 // instruction reads one constant from the scalar registers, so an fma of two
 // constants needs the other one in a vector register, where the compiler would
 // move it again in every round of a loop.
@@ -110,6 +112,16 @@ struct Bm {
     const BmTables* t;
     double ang_a3, ang_b2;
 };
+
+// Entry i of the tables as it is kept in LDS (halving is exact).
+__device__ __forceinline__ uint4 staged_entry(int i, uint4 v)
+{
+    if (i < kLogTableSize) return v;
+    AngleEntry t = __builtin_bit_cast(AngleEntry, v);
+    t.c *= 0.5;
+    t.s *= 0.5;
+    return __builtin_bit_cast(uint4, t);
+}
 
 // Copy both tables into LDS; every thread of the workgroup must call it (it
 // ends with a barrier).  With a BLOCK-thread workgroup each thread issues all
@@ -130,9 +142,10 @@ __device__ __forceinline__ Bm stage_bm_tables()
             if ((r + 1) * BLOCK <= kWords || threadIdx.x + r * BLOCK < kWords) v[r] = src[threadIdx.x + r * BLOCK];
 #pragma unroll
         for (int r = 0; r < kPer; ++r)
-            if ((r + 1) * BLOCK <= kWords || threadIdx.x + r * BLOCK < kWords) dst[threadIdx.x + r * BLOCK] = v[r];
+            if ((r + 1) * BLOCK <= kWords || threadIdx.x + r * BLOCK < kWords)
+                dst[threadIdx.x + r * BLOCK] = staged_entry(threadIdx.x + r * BLOCK, v[r]);
     } else {
-        for (int i = threadIdx.x; i < kWords; i += blockDim.x) dst[i] = src[i];
+        for (int i = threadIdx.x; i < kWords; i += blockDim.x) dst[i] = staged_entry(i, src[i]);
     }
     __syncthreads();
     Bm bm = {&tb, kAngA3, kAngB2};
@@ -173,22 +186,26 @@ __device__ __forceinline__ double bm_log_term(uint32_t a, const Bm& tb)
     return __builtin_fma(r, q, base);
 }
 
-// rho = sqrt(L) for L > 0: hardware reciprocal square root (2^-24) and one
-// Goldschmidt step (2^-47).
-__device__ __forceinline__ double bm_sqrt(double L)
+// 2 rho = 2 sqrt(L) for L > 0: hardware reciprocal square root y (2^-24) and
+// one Newton step, (L y) (3 - L y^2), to 2^-47; `scale` multiplies it on the
+// way.  Leaving the factor two to the circle's table saves an instruction a
+// pair against sqrt(L) itself.
+__device__ __forceinline__ double bm_radius2(uint32_t a, const Bm& tb)
 {
+    const double L = bm_log_term(a, tb);
     const double y = __builtin_amdgcn_rsq(L);
     const double g = L * y;
-    const double h = 0.5 * y;
-    return __builtin_fma(g, __builtin_fma(-g, h, 0.5), g);
+    return g * __builtin_fma(-g, y, 3.0);
 }
-
-__device__ __forceinline__ double bm_radius(uint32_t a, const Bm& tb)
+__device__ __forceinline__ double bm_radius2(uint32_t a, const Bm& tb, double scale)
 {
-    return bm_sqrt(bm_log_term(a, tb));
+    const double L = bm_log_term(a, tb);
+    const double y = __builtin_amdgcn_rsq(L);
+    const double g = L * y;
+    return (g * scale) * __builtin_fma(-g, y, 3.0);
 }
 
-// (cos, sin)(theta) for theta = 2 pi m 2^-24, m = (b >> 8) + 1 in [1, 2^24],
+// (cos, sin)(theta) / 2 for theta = 2 pi m 2^-24, m = (b >> 8) + 1 in [1, 2^24],
 // as a rotation from the nearest of 512 table angles: i = round(m / 2^15)
 // mod 512, offset x = m - 2^15 round(m / 2^15) in [-2^14, 2^14), delta =
 // x 2 pi 2^-24.  sin delta (degree 5) and cos delta (degree 4) are Taylor
@@ -197,7 +214,7 @@ __device__ __forceinline__ double bm_radius(uint32_t a, const Bm& tb)
 // reduces to +-sin delta and keeps its relative accuracy; the table's signed
 // zeros make the quarter-turn angles come out as in an exact quadrant
 // reduction.  Relative error below 2^-50 over all 2^24 inputs.
-__device__ __forceinline__ void bm_angle(uint32_t b, const Bm& tb, double& cos_t, double& sin_t)
+__device__ __forceinline__ void bm_half_angle(uint32_t b, const Bm& tb, double& cos_t, double& sin_t)
 {
     // Adding 0x100 to b cannot carry out of its low byte, so bits 8..31 of
     // b + 0x100 are m mod 2^24 (m = 2^24 wraps to 0, the same angle); x is
@@ -218,11 +235,22 @@ __device__ __forceinline__ void bm_angle(uint32_t b, const Bm& tb, double& cos_t
 // fp32(rho sin theta).
 __device__ __forceinline__ void bm_pair(uint32_t a, uint32_t b, const Bm& tb, float& z_even, float& z_odd)
 {
-    const double rho = bm_radius(a, tb);
+    const double rho = bm_radius2(a, tb);
     double c, s;
-    bm_angle(b, tb, c, s);
+    bm_half_angle(b, tb, c, s);
     z_even = (float)(rho * c);
     z_odd = (float)(rho * s);
+}
+
+// The pair scaled and added to fp64 sums, without the rounding to fp32 between.
+__device__ __forceinline__ void bm_pair_add(uint32_t a, uint32_t b, const Bm& tb, double scale, double& even,
+                                            double& odd)
+{
+    const double rho = bm_radius2(a, tb, scale);
+    double c, s;
+    bm_half_angle(b, tb, c, s);
+    even = __builtin_fma(rho, c, even);
+    odd = __builtin_fma(rho, s, odd);
 }
 
 // Four normals of block q: positions 4q .. 4q+3 (domain 0 is the noise).
@@ -246,6 +274,18 @@ __device__ __forceinline__ void normals8(uint32_t k0, uint32_t k1, Q q, const Bm
     bm_pair(x.z, x.w, tb, z[2], z[3]);
     bm_pair(y.x, y.y, tb, z[4], z[5]);
     bm_pair(y.z, y.w, tb, z[6], z[7]);
+}
+
+// acc[e] += scale times the normal of position 4q + e, N = 4 or 8 of them.
+template <int N, typename Q>
+__device__ __forceinline__ void add_normals(uint32_t k0, uint32_t k1, Q q, const Bm& tb, double scale, double acc[N])
+{
+#pragma unroll
+    for (int h = 0; h < N / 4; ++h) {
+        const Words4 x = stream_block(k0, k1, 0u, (Q)(q + h));
+        bm_pair_add(x.x, x.y, tb, scale, acc[4 * h + 0], acc[4 * h + 1]);
+        bm_pair_add(x.z, x.w, tb, scale, acc[4 * h + 2], acc[4 * h + 3]);
+    }
 }
 
 // ------------------------------------------------------------------ bf16 --

@@ -382,7 +382,14 @@ __global__ __launch_bounds__(kBlock) void k_stage_master(StreamArgs a)
 // ----------------------------------------------------------------- update --
 // theta_S += step * sum_u c_u eps_u, c_u = sum over members of stream u of
 // sign * rnorm.  Each thread reads its unit of weights once, regenerates every
-// stream's noise for it in registers, accumulates in fp32 and writes once.
+// stream's noise for it in registers, accumulates in fp64 and writes once.
+//
+// Bound by the VALU.  fp64 runs at the rate of fp32 here, so the sums stay in
+// fp64 from the Box-Muller products on: c rho cos and c rho sin are one product
+// for the pair and one fma for each sum, where normals rounded to fp32 take a
+// product, a conversion and an fma each.  504,654,080 bf16 positions,
+// 30 streams: 226 instead of 242 VALU instructions per 8 normals, 11.92 instead
+// of 12.27 ms; 64 mirrored pairs on 251 M with a master, 10.46 and 10.75 ms.
 
 // Stream coefficients, and a bit for each stream that contributes: those with
 // a coefficient other than zero.  A mirrored pair with equal rewards cancels to
@@ -391,9 +398,9 @@ __global__ __launch_bounds__(kBlock) void k_stage_master(StreamArgs a)
 // that is never -0, so leaving the stream's noise ungenerated changes no bit.
 // 16 mirrored pairs with success / failure rewards on 9.4 M bf16 weights: 71 us
 // against 143 us; 64 pairs with rewards averaged over 8 rollouts, 251 M weights
-// with a master: 10.7 against 13.2 ms.
+// with a master: 10.5 against 13.2 ms.
 struct Streams {
-    float coef[kMaxMembers];
+    double coef[kMaxMembers];
     uint64_t some[kMaxMembers / 64 + 1];   // a range may start behind the last word
 };
 
@@ -417,9 +424,8 @@ __device__ __forceinline__ const Streams* fold_members(const MemberTable& t, int
     __syncthreads();
     double c = 0.0;
     for (int i = i0; i < i1; ++i) c += (double)value[i];
-    const float coef = (float)c;
-    st.coef[u] = coef;
-    const uint64_t some = __builtin_amdgcn_ballot_w64(u < n_streams && !(coef == 0.0f));   // a NaN counts
+    st.coef[u] = c;
+    const uint64_t some = __builtin_amdgcn_ballot_w64(u < n_streams && !(c == 0.0));       // a NaN counts
     if ((u & 63) == 0) st.some[u / 64] = some;
     __syncthreads();
     return &st;
@@ -432,20 +438,19 @@ template <int N, typename Q>
 __device__ __forceinline__ void accumulate_streams(const MemberTable& t, const Streams* st, int s0, int s1, Q q,
                                                    const Bm& tb, float acc[N])
 {
+    double sum[N];
 #pragma unroll
-    for (int e = 0; e < N; ++e) acc[e] = 0.0f;
+    for (int e = 0; e < N; ++e) sum[e] = 0.0;
     uint64_t bits = (uint64_t)wave_uniform((int64_t)st->some[s0 / 64]) >> (s0 & 63);   // from stream s on
     for (int s = s0; s < s1; ++s) {
         const bool some = bits & 1u;
         bits >>= 1;
         if (((s + 1) & 63) == 0 && s + 1 < s1) bits = (uint64_t)wave_uniform((int64_t)st->some[(s + 1) / 64]);
         if (!some) continue;
-        const float c = st->coef[s];
-        float z[N];
-        unit_normals<N, Q>(t.seed_lo[s], t.seed_hi[s], q, tb, z);
-#pragma unroll
-        for (int e = 0; e < N; ++e) acc[e] = __builtin_fmaf(c, z[e], acc[e]);
+        add_normals<N, Q>(t.seed_lo[s], t.seed_hi[s], q, tb, st->coef[s], sum);
     }
+#pragma unroll
+    for (int e = 0; e < N; ++e) acc[e] = (float)sum[e];
 }
 
 template <typename T, bool MASTER, typename Q, int ADDR>
@@ -2036,11 +2041,11 @@ __global__ __launch_bounds__(kBlock) void k_debug_bm_grid(uint32_t m0, int64_t n
     const Bm tb = stage_bm_tables<kBlock>();
     for (int64_t k = global_tid(); k < n; k += grid_stride()) {
         const uint32_t word = (m0 + (uint32_t)k - 1u) << 8;
-        if (rho) rho[k] = bm_radius(word, tb);
+        if (rho) rho[k] = 0.5 * bm_radius2(word, tb);
         double cc, ss;
-        bm_angle(word, tb, cc, ss);
-        if (c) c[k] = cc;
-        if (s) s[k] = ss;
+        bm_half_angle(word, tb, cc, ss);
+        if (c) c[k] = 2.0 * cc;
+        if (s) s[k] = 2.0 * ss;
     }
 }
 

@@ -1662,25 +1662,57 @@ __global__ __launch_bounds__(kBlock) void k_part_tables(PartitionArgs a)
     a.tables[t] = (uint16_t)(y.x & mask);
 }
 
-// One workgroup of 16 waves per CU, its LDS filled with the tables of G
-// rounds at a time (G 2^h uint16 = 128 KiB at most: all 8 rounds for h <= 13,
-// 1 for h = 16), each wave walking a contiguous range of elements in
-// kPartSlots slots per lane.  Every pass takes each slot one step further;
-// slots that have arrived in [0, d) give their bucket and take the next
-// element of the range.  Bound by the LDS (random 2-byte reads) and, for
-// h > 13, by refilling it from L2 once per pass: the more slots a pass moves,
-// the less of that.  1,009,308,160 elements (h = 15): 3.2 ms, against 8.8 ms
-// with Philox evaluated in each step.
-template <int G> constexpr int kPartSlots = G == 1 ? 32 : G == 8 ? 16 : 24;
+// One workgroup of 16 waves per CU, 128 KiB of its LDS filled with tables,
+// each wave walking a contiguous range of elements in kPartSlots slots per
+// lane.  Every pass takes each slot one step further, G rounds per stage; slots
+// that have arrived in [0, d) give their bucket and take the next element of
+// the range.  h <= 13: all 8 rounds fit (G = 8).  h = 14, 15: a stage's tables
+// take half of the space (G = 2, 1), and the next stage's are loaded straight
+// into the other half during the look-ups, with one barrier a stage.  h = 16:
+// one round fills it (G = 1), and the waves wait for each refill.  Bound by the
+// LDS (random 2-byte reads); the more slots a pass moves, the less the refills
+// from L2 count.  1,009,308,160 elements (h = 15): 8.8 ms with Philox evaluated
+// in each step, 3.2 ms with two rounds per refill and the waves waiting for it,
+// 2.63 ms so (2.6 also without the refills: they are hidden).
+template <int H> constexpr int kPartRounds = H == 13 ? 8 : H == 14 ? 2 : 1;
+template <int H> constexpr int kPartSlots = H == 13 ? 16 : H == 14 ? 24 : 32;
 constexpr int kTableWaves = 16;
 constexpr int kTableGroups = 256;         // workgroups: one per CU
 constexpr int kTableElems = 1 << 16;      // uint16 entries in LDS
 
-template <int G>
+// Half of the LDS (64 KiB) from `src`, 64 bytes per thread, without a register
+// in between: a wave's 64 lanes write 1 KiB at m0 and the offset.  The caller
+// waits with lds_half_wait before the data is read, the buffer reused, or the
+// kernel ends.  Written out because the compiler would wait for the transfer
+// before any other LDS read.
+__device__ __forceinline__ void lds_half_load(const uint16_t* src, uint16_t* half)
+{
+    static_assert(kTableElems / 2 * 2 == 64 * kTableWaves * 64, "64 bytes per thread");
+    typedef __attribute__((address_space(3))) uint16_t Lds;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x & 63;
+    const uint32_t to = (uint32_t)(uintptr_t)(Lds*)(half + wave * 2048);
+    const uint16_t* from = src + wave * 2048 + lane * 8;
+    asm volatile("s_mov_b32 m0, %0\n\t"
+                 "s_nop 0\n\t"
+                 "global_load_lds_dwordx4 %1, off\n\t"
+                 "global_load_lds_dwordx4 %1, off offset:1024\n\t"
+                 "global_load_lds_dwordx4 %1, off offset:2048\n\t"
+                 "global_load_lds_dwordx4 %1, off offset:3072"
+                 :: "s"(to), "v"(from) : "memory", "m0");
+}
+__device__ __forceinline__ void lds_half_wait()
+{
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+
+// H: the tables' 2^h arguments, 13 for all h <= 13.
+template <int H>
 __global__ __launch_bounds__(64 * kTableWaves) void k_part_bucket_table(PartitionArgs a)
 {
     __shared__ __attribute__((aligned(16))) uint16_t tab[kTableElems];
-    constexpr int kSlots = kPartSlots<G>;
+    constexpr int kSlots = kPartSlots<H>, G = kPartRounds<H>, kStages = kFeistelRounds / G;
+    constexpr bool kHalves = H == 14 || H == 15;
+    static_assert(!kHalves || (G << H == kTableElems / 2 && kStages % 2 == 0), "a stage fills half of the LDS");
     const int lane = threadIdx.x & 63;
     const int64_t wave = (int64_t)blockIdx.x * kTableWaves + __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
     constexpr int64_t kWaves = (int64_t)kTableGroups * kTableWaves;
@@ -1705,10 +1737,17 @@ __global__ __launch_bounds__(64 * kTableWaves) void k_part_bucket_table(Partitio
         e[i] = 64 * i + lane;
         x[i] = halves(e[i]);
     }
+    if (kHalves) lds_half_load(a.tables, tab);
     for (int pass = 0;; ++pass) {
 #pragma unroll 1
-        for (int g = 0; g < kFeistelRounds / G; ++g) {
-            if (G < kFeistelRounds || pass == 0) {
+        for (int g = 0; g < kStages; ++g) {
+            const uint16_t* stage = tab;
+            if (kHalves) {
+                lds_half_wait();                                   // this stage's tables, as far as this wave loads them
+                __syncthreads();                                   // all of them, and no wave reads the other half any more
+                stage = tab + (g & 1) * (kTableElems / 2);
+                lds_half_load(a.tables + ((size_t)((g + 1) % kStages * G) << h), tab + (~g & 1) * (kTableElems / 2));
+            } else if (G < kFeistelRounds || pass == 0) {
                 if (G < kFeistelRounds) __syncthreads();           // every wave is done with the last tables
                 const V4u* src = reinterpret_cast<const V4u*>(a.tables + ((size_t)(g * G) << h));
                 for (uint32_t v = threadIdx.x; v < (uint32_t)(G << h) / 8u; v += 64 * kTableWaves)
@@ -1717,7 +1756,7 @@ __global__ __launch_bounds__(64 * kTableWaves) void k_part_bucket_table(Partitio
             }
 #pragma unroll
             for (int r = 0; r < G; ++r) {
-                const uint16_t* t = tab + ((uint32_t)r << h);
+                const uint16_t* t = stage + ((uint32_t)r << h);
 #pragma unroll
                 for (int i0 = 0; i0 < kSlots; i0 += 8) {
                     uint32_t f[8];
@@ -1753,6 +1792,7 @@ __global__ __launch_bounds__(64 * kTableWaves) void k_part_bucket_table(Partitio
         left = left && !stuck;
         if (G < kFeistelRounds ? !__syncthreads_or(left) : __builtin_amdgcn_ballot_w64(left) == 0) break;
     }
+    if (kHalves) lds_half_wait();                                  // for the load that no stage reads
 }
 
 // Bucket counts of every tile for the table path, one wave per tile.  Up to 8
@@ -2404,10 +2444,10 @@ void partition_tables(const PartitionArgs& a, hipStream_t s)
     const dim3 grid(kTableGroups), block(64 * kTableWaves);
     const unsigned entries = (unsigned)kFeistelRounds << a.half_bits;
     hipLaunchKernelGGL(k_part_tables, dim3((entries + kBlock - 1) / kBlock), dim3(kBlock), 0, s, a);
-    if (a.half_bits <= 13) hipLaunchKernelGGL((k_part_bucket_table<8>), grid, block, 0, s, a);
-    else if (a.half_bits == 14) hipLaunchKernelGGL((k_part_bucket_table<4>), grid, block, 0, s, a);
-    else if (a.half_bits == 15) hipLaunchKernelGGL((k_part_bucket_table<2>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((k_part_bucket_table<1>), grid, block, 0, s, a);
+    if (a.half_bits <= 13) hipLaunchKernelGGL((k_part_bucket_table<13>), grid, block, 0, s, a);
+    else if (a.half_bits == 14) hipLaunchKernelGGL((k_part_bucket_table<14>), grid, block, 0, s, a);
+    else if (a.half_bits == 15) hipLaunchKernelGGL((k_part_bucket_table<15>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_part_bucket_table<16>), grid, block, 0, s, a);
     const dim3 tiles((unsigned)((a.n_tiles + kBlock / 64 - 1) / (kBlock / 64)));
     if (a.K <= 8) hipLaunchKernelGGL((k_part_count<3>), tiles, dim3(kBlock), 0, s, a);
     else hipLaunchKernelGGL((k_part_count<8>), tiles, dim3(kBlock), 0, s, a);

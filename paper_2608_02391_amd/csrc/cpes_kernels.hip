@@ -1652,14 +1652,15 @@ __global__ __launch_bounds__(64 * kPartWaves) void k_part_bucket(PartitionArgs a
 // arguments (h <= 16 for d <= 2^32) and 8 rounds: k_part_tables evaluates all
 // of them once, 8 * 2^h uint16 values (at most 1 MiB), and a step of a walk
 // becomes eight LDS look-ups instead of eight Philox blocks.  The tables lie
-// in the map that the scatter writes afterwards.
+// in the map that the scatter writes afterwards.  Below h = 16 the values are
+// kept doubled: a half of a walk is then the byte offset of its look-up.
 __global__ __launch_bounds__(kBlock) void k_part_tables(PartitionArgs a)
 {
     const uint32_t t = blockIdx.x * kBlock + threadIdx.x;
     if (t >= (uint32_t)kFeistelRounds << a.half_bits) return;
     const uint32_t mask = (1u << a.half_bits) - 1u;
     const Words4 y = philox4x32_10(t & mask, t >> a.half_bits, 3u, 0u, (uint32_t)a.seed, (uint32_t)(a.seed >> 32));
-    a.tables[t] = (uint16_t)(y.x & mask);
+    a.tables[t] = (uint16_t)((y.x & mask) << (a.half_bits < 16 ? 1 : 0));
 }
 
 // One workgroup of 16 waves per CU, 128 KiB of its LDS filled with tables,
@@ -1673,7 +1674,7 @@ __global__ __launch_bounds__(kBlock) void k_part_tables(PartitionArgs a)
 // LDS (random 2-byte reads); the more slots a pass moves, the less the refills
 // from L2 count.  1,009,308,160 elements (h = 15): 8.8 ms with Philox evaluated
 // in each step, 3.2 ms with two rounds per refill and the waves waiting for it,
-// 2.63 ms so (2.6 also without the refills: they are hidden).
+// 2.52 ms so (without the refills it is no faster: they are hidden).
 template <int H> constexpr int kPartRounds = H == 13 ? 8 : H == 14 ? 2 : 1;
 template <int H> constexpr int kPartSlots = H == 13 ? 16 : H == 14 ? 24 : 32;
 constexpr int kTableWaves = 16;
@@ -1719,19 +1720,25 @@ __global__ __launch_bounds__(64 * kTableWaves) void k_part_bucket_table(Partitio
     const int64_t range = (a.d + kWaves - 1) / kWaves;             // at most 2^20 elements
     const int64_t first = wave * range;
     const int n = first >= a.d ? 0 : a.d - first < range ? (int)(a.d - first) : (int)range;
-    const uint32_t last = (uint32_t)(a.d - 1);
-    const int h = a.half_bits;
+    constexpr int kDouble = H < 16 ? 1 : 0;
+    const int h = H == 13 ? a.half_bits : H;
     const uint32_t mask = (1u << h) - 1u;
     uint8_t* bucket = a.bucket + first;
-    // A slot holds the halves (L, R) of its walk as L << 16 | R: a round is
-    // then a rotation by 16 and an xor with the looked-up value.
-    auto halves = [&](int v) -> uint32_t {
-        const uint32_t i = (uint32_t)first + (uint32_t)v;
-        return ((i >> h) << 16) | (i & mask);
+    // A slot holds the halves (L, R) of its walk, doubled like the tables, as
+    // L << 16 | R: a round is then a rotation by 16 and an xor with the
+    // looked-up value, and R the offset to look up.
+    // (Elements behind the range, which a slot without work holds, are masked into the tables too.)
+    auto split = [&](uint32_t i) -> uint32_t {
+        return (((i >> h) & mask) << (16 + kDouble)) | ((i & mask) << kDouble);
+    };
+    auto halves = [&](int v) -> uint32_t { return split((uint32_t)first + (uint32_t)v); };
+    const uint32_t x_last = split((uint32_t)(a.d - 1));
+    auto look_up = [&](const uint16_t* t, uint32_t x) -> uint32_t {
+        return *reinterpret_cast<const uint16_t*>(reinterpret_cast<const char*>(t) + ((x & 0xFFFFu) << (1 - kDouble)));
     };
     uint32_t x[kSlots];
     int e[kSlots];
-    int next = 64 * kSlots;
+    int next = 64 * kSlots, missing = n;                           // buckets not written yet
 #pragma unroll
     for (int i = 0; i < kSlots; ++i) {
         e[i] = 64 * i + lane;
@@ -1761,7 +1768,7 @@ __global__ __launch_bounds__(64 * kTableWaves) void k_part_bucket_table(Partitio
                 for (int i0 = 0; i0 < kSlots; i0 += 8) {
                     uint32_t f[8];
 #pragma unroll
-                    for (int i = 0; i < 8; ++i) f[i] = t[x[i0 + i] & 0xFFFFu];
+                    for (int i = 0; i < 8; ++i) f[i] = look_up(t, x[i0 + i]);
 #pragma unroll
                     for (int i = 0; i < 8; ++i)
                         x[i0 + i] = __builtin_amdgcn_alignbit(x[i0 + i], x[i0 + i], 16) ^ f[i];
@@ -1774,22 +1781,24 @@ __global__ __launch_bounds__(64 * kTableWaves) void k_part_bucket_table(Partitio
             for (int v = lane; v < n; v += 64) bucket[v] = 0;
             if (a.status && lane == 0) atomicOr(a.status, 1);
         }
-        bool left = false;
 #pragma unroll
         for (int i = 0; i < kSlots; ++i) {
-            const uint32_t y = ((x[i] >> 16) << h) | (x[i] & 0xFFFFu);
-            const bool done = y <= last;
-            if (done && e[i] < n && !stuck) bucket[e[i]] = (uint8_t)bucket_of<uint32_t>(y, a);
+            const bool done = x[i] <= x_last;                      // slots compare like the elements they hold
             const uint64_t m = __builtin_amdgcn_ballot_w64(done);
+            const bool mine = e[i] < n;
+            missing -= __popcll(m & __builtin_amdgcn_ballot_w64(mine));
+            if (done && mine && !stuck) {
+                const uint32_t y = ((x[i] >> (16 + kDouble)) << h) | ((x[i] & 0xFFFFu) >> kDouble);
+                bucket[(uint32_t)e[i]] = (uint8_t)bucket_of<uint32_t>(y, a);
+            }
             if (done) {
                 e[i] = next + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
                 x[i] = halves(e[i]);
             }
             next += __popcll(m);
-            left |= e[i] < n;
             __builtin_amdgcn_sched_barrier(0);
         }
-        left = left && !stuck;
+        const bool left = missing > 0 && !stuck;
         if (G < kFeistelRounds ? !__syncthreads_or(left) : __builtin_amdgcn_ballot_w64(left) == 0) break;
     }
     if (kHalves) lds_half_wait();                                  // for the load that no stage reads

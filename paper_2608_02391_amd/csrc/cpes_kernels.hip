@@ -2182,12 +2182,15 @@ int64_t grid_for(int64_t work_items, int64_t cap = kMaxGrid)
 }
 
 // Workgroups of a noise kernel on `items` units of a contiguous or chunked
-// subspace.  Up to 8,192 of them take one unit per thread.  Larger launches
+// subspace (threads of kBlock).  Up to 8,192 of them take one unit per thread.  Larger launches
 // loop: the tables are staged once per workgroup, so a workgroup wants several
 // units, but with few, long workgroups the launch ends on the slowest CU
 // (504,654,080 positions, 16 streams: 8,192 workgroups 6.64 ms, one workgroup
 // per four units of a thread 6.50 ms, per three 6.46 ms, per two 6.51 ms; one
-// perturbation 566, 558, 548 and 553 us).
+// perturbation 566, 558, 548 and 553 us).  The same rule serves perturbations
+// through ascending maps, in workgroups of two (126,163,520 positions, int64
+// map, from the backup, with its restore: 1,811 us with 4,096 workgroups of 512
+// threads, 1,755 us with one per three tiles of a wave, 1,774 us per eight).
 int64_t noise_grid_cap(int64_t items)
 {
     const int64_t blocks = (items + kBlock - 1) / kBlock;
@@ -2244,8 +2247,8 @@ template <typename T, int AUX, typename Q>
 hipError_t perturb_t(int addr, const StreamArgs& a, hipStream_t s)
 {
     if (std::is_same<T, uint16_t>::value && a.dense) {
-        const dim3 grid((unsigned)std::min<int64_t>(std::max<int64_t>((dense_threads(a.length) + kDenseBlock - 1) / kDenseBlock, 1),
-                                                    kRngMaxGrid / 2));
+        const int64_t threads = dense_threads(a.length);
+        const dim3 grid((unsigned)std::min((threads + kDenseBlock - 1) / kDenseBlock, noise_grid_cap(threads) / (kDenseBlock / kBlock)));
         if (addr == kGather) hipLaunchKernelGGL((k_perturb_dense<AUX, Q, kGather>), grid, dim3(kDenseBlock), 0, s, a);
         else if (addr == kGather32) hipLaunchKernelGGL((k_perturb_dense<AUX, Q, kGather32>), grid, dim3(kDenseBlock), 0, s, a);
         if (addr == kGather || addr == kGather32) return hipGetLastError();

@@ -165,3 +165,36 @@ def test_any_element_alignment(orc, T, length, dtype, layout):
     for shift, side in ((1, 0), (0, 1), (3, 5), (7, 2)):
         for a, b in zip(want, passes(shift, side)):
             assert T.equal(a, b)
+
+
+@pytest.mark.parametrize("kind", ["contiguous", "map", "step"])
+@pytest.mark.parametrize("dtype,n", [(S.F32, 1), (S.F32, 256), (S.BF16, 256)])
+def test_update_sums_in_64_bits(orc, T, kind, dtype, n):
+    """From zero weights with a step of 1 the update is the noise sum rounded
+    once (twice for bf16): the oracle's 64-bit factors give it, to one rounding
+    to fp32 and the 2^-44 of the device's factors.  A sum of 256 terms in fp32
+    is some ten roundings off."""
+    length = 4 * 515 + 3
+    seeds, c = [900 + u for u in range(n)], np.random.default_rng(n).normal(size=n).astype(np.float32)
+    want, size = np.zeros(length), np.zeros(length)
+    for seed, cu in zip(seeds, c):
+        x = orc.blocks(seed, 0, 0, (length + 3) // 4).reshape(-1, 2)
+        rho, (co, si) = orc.bm_radius_many(x[:, 0]), orc.bm_angle_many(x[:, 1])
+        z = np.stack([rho * co, rho * si], axis=1).reshape(-1)[:length]
+        want += float(cu) * z
+        size += abs(float(cu)) * np.abs(z)
+    w = T.zeros(4 * length, dtype=T.bfloat16 if dtype == S.BF16 else T.float32, device="cuda")
+    at = np.arange(length)
+    if kind == "map":
+        at = np.sort(np.random.default_rng(3).permutation(4 * length)[:length]).astype(np.int64)
+    if kind == "step":
+        cp.cpes_update_step(w, [0, length], seeds, [1] * n, [0] * n, to_dev(c), float(n), [1.0], cp.SCALE_ALPHA_OVER_N)
+    else:
+        sub = cp.subspace(0, length, to_dev(at) if kind == "map" else None)
+        cp.cpes_update(w, sub, seeds, [1] * n, to_dev(c), float(n), 1.0, cp.SCALE_ALPHA_OVER_N)
+    got = w.double().cpu().numpy()
+    rounding = 2.0 ** -24 if dtype == S.F32 else 2.0 ** -8 * 1.01
+    assert np.all(np.abs(got[at] - want) <= rounding * np.abs(want) + 2.0 ** -44 * size)
+    rest = np.ones(4 * length, dtype=bool)
+    rest[at] = False
+    assert not got[rest].any()

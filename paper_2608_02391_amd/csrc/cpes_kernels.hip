@@ -834,16 +834,18 @@ __device__ __forceinline__ void dense_entries(const int64_t* index, int64_t offs
 
 // Window transfers: lines [lo, hi] of w to and from the wave's LDS buffer,
 // one 16-byte vector per lane per step, non-temporal (the weights far exceed
-// the caches); the element path covers a window running past numel.
+// the caches); the element path covers a window running past numel.  Lines
+// count from the first weight, which may lie at any element's address.
 __device__ __forceinline__ void window_load(const uint16_t* w, int64_t numel, const DenseTile& d, uint16_t* buf,
                                             int lane)
 {
     const int64_t base = d.lo * kLineElems, nvec = (d.hi - d.lo + 1) * (kLineElems / 8);
     const bool whole = base + nvec * 8 <= numel;
+    typedef Vec16<uint16_t>::type V;
     for (int64_t v = lane; v < nvec; v += 64) {
         if (whole) {
             *reinterpret_cast<V4u*>(buf + 8 * v) =
-                __builtin_nontemporal_load(reinterpret_cast<const V4u*>(w + base) + v);
+                __builtin_nontemporal_load(reinterpret_cast<const V*>(w + base) + v);
         } else {
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
@@ -858,10 +860,11 @@ __device__ __forceinline__ void window_store(uint16_t* w, int64_t numel, const D
 {
     const int64_t base = d.lo * kLineElems, nvec = (d.hi - d.lo + 1) * (kLineElems / 8);
     const bool whole = base + nvec * 8 <= numel;
+    typedef Vec16<uint16_t>::type V;
     for (int64_t v = lane; v < nvec; v += 64) {
         if (whole) {
             __builtin_nontemporal_store(*reinterpret_cast<const V4u*>(buf + 8 * v),
-                                        reinterpret_cast<V4u*>(w + base) + v);
+                                        reinterpret_cast<V*>(w + base) + v);
         } else {
 #pragma unroll
             for (int k = 0; k < 8; ++k) {

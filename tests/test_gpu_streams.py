@@ -113,10 +113,12 @@ def test_noise_blocks_around_2_to_32(orc, T, noise0, dtype, layout):
 
 @pytest.mark.parametrize("length", [1, 7, 8, 9, 2047, 2048, 2049, 70001])
 @pytest.mark.parametrize("dtype", [S.BF16, S.F32])
-@pytest.mark.parametrize("layout", ["contiguous", "chunk", "map"])
+@pytest.mark.parametrize("layout", ["contiguous", "chunk", "map", "ascending", "ascending32"])
 def test_any_element_alignment(orc, T, length, dtype, layout):
     """Weights, backup and master each at their own element offset from a
-    vector boundary: the same bits as from aligned copies."""
+    vector boundary: the same bits as from aligned copies.  Through ascending
+    maps (one entry in four: whole-line windows) the map starts at an odd
+    entry too."""
     C = 256
     numel = 4 * length + 8 * C
     base = S.host_weights(numel + 8, dtype, length)
@@ -126,8 +128,9 @@ def test_any_element_alignment(orc, T, length, dtype, layout):
         chunks = to_dev(np.random.default_rng(2).permutation(numel // C)[:length // C + 1].astype(np.int64))
         make = lambda off: cp.subspace(0, length, chunks, C)
     else:
-        index = to_dev(np.sort(np.random.default_rng(2).permutation(numel)[:length + 3]).astype(np.int64))
-        make = lambda off: cp.subspace(3, length, index)
+        index = np.sort(np.random.default_rng(2).permutation(numel)[:length + 3])
+        index = to_dev(index.astype(np.int32 if layout == "ascending32" else np.int64))
+        make = lambda off: cp.subspace(3, length, index, ascending=layout != "map")
     tdt = T.bfloat16 if dtype == S.BF16 else T.float32
     r = to_dev(np.array([0.5, -1.0], dtype=np.float32))
 

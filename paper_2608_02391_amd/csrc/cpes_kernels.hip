@@ -1582,7 +1582,7 @@ __global__ void k_status_zero(int32_t* status)
 // a chunk list has a few thousand ids, and one wave per tile would leave
 // almost every CU idle behind a few waves that take 2,048 elements one after
 // the other (2,304 ids: 62 us with one wave per tile, 27 us with four, 29 us
-// with sixteen; 2^22: 71, 66 and 72 us; 2^24 + 7: 702, 833 and 1,548 us).
+// with sixteen; 2^22: 71, 66 and 72 us).
 constexpr int kPartWaves = 4;
 template <int WPT> constexpr int kPartTiles = kPartWaves / WPT;          // tiles per workgroup
 template <int WPT> constexpr int kPartSub = (int)kTile / WPT;            // elements per wave
@@ -2468,14 +2468,15 @@ void partition_tables(const PartitionArgs& a, hipStream_t s)
     else hipLaunchKernelGGL((k_part_count<8>), tiles, dim3(kBlock), 0, s, a);
 }
 
+// WPT: kPartTableMin draws the line between shared tiles (4) and large partitions (1).
 template <int WPT>
-void partition_passes(const PartitionArgs& a, bool tables, hipStream_t s)
+void partition_passes(const PartitionArgs& a, hipStream_t s)
 {
     const dim3 grid((unsigned)((a.n_tiles + kPartTiles<WPT> - 1) / kPartTiles<WPT>)), block(64 * kPartWaves);
     const int64_t n_counts = (int64_t)a.K * a.n_tiles;
     const unsigned scan_blocks = (unsigned)((n_counts + kScanChunk - 1) / kScanChunk);
-    if (tables) partition_tables(a, s);
-    else if (a.d <= (1ll << 32)) hipLaunchKernelGGL((k_part_bucket<uint32_t, WPT>), grid, block, 0, s, a);
+    if constexpr (WPT == 4) hipLaunchKernelGGL((k_part_bucket<uint32_t, WPT>), grid, block, 0, s, a);
+    else if (a.tables) partition_tables(a, s);
     else hipLaunchKernelGGL((k_part_bucket<uint64_t, WPT>), grid, block, 0, s, a);
     if (scan_blocks > 1) {
         hipLaunchKernelGGL(k_scan_reduce, dim3(scan_blocks), dim3(kBlock), 0, s, a.counts, n_counts, a.block_sums);
@@ -2492,15 +2493,15 @@ hipError_t launch_partition(const PartitionArgs& args, hipStream_t s)
 {
     PartitionArgs a = args;
     if (a.status) hipLaunchKernelGGL(k_status_zero, dim3(1), dim3(1), 0, s, a.status);
-    const bool tables = a.d >= kPartTableMin && a.d <= (1ll << 32);
-    if (tables) {
+    a.tables = nullptr;
+    if (a.d >= kPartTableMin && a.d <= (1ll << 32)) {
         // the first 16-byte boundary of the output map: 8 * 2^h uint16 entries
         // and 15 bytes fit its d > 2^(2h - 2) entries of at least 4 bytes
         const uintptr_t out = a.index32 ? (uintptr_t)a.index32 : (uintptr_t)a.index;
         a.tables = reinterpret_cast<uint16_t*>((out + 15) & ~(uintptr_t)15);
     }
-    if (a.d < kPartTableMin) partition_passes<4>(a, false, s);
-    else partition_passes<1>(a, tables, s);
+    if (a.d < kPartTableMin) partition_passes<4>(a, s);
+    else partition_passes<1>(a, s);
     return hipGetLastError();
 }
 

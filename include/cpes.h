@@ -301,7 +301,7 @@ CPES_API int cpes_stage_master(const void* w_dev, int64_t numel, int dtype, cons
 /*
  * cpes_normalize_rewards -- reward standardisation.
  *   CPES_NORM_Z:    Eq. (5) / Eq. (12): mu = sum r / n, s = sqrt(sum (r - mu)^2 / n)
- *                   (population std, sums in fp64 in index order);
+ *                   (population std, sums in fp64 in a fixed order);
  *                   out = (r - mu) / s, or 0 for every member when s == 0.
  *   CPES_NORM_RANK: centred average rank a / (n - 1) - 1/2 with a the 0-based
  *                   rank and ties sharing the mean of their ranks; 0 when n == 1.
@@ -418,10 +418,11 @@ CPES_API int cpes_debug_prp(uint64_t seed, int64_t d, int32_t K, int64_t i0, int
 
 /* RNG-only throughput probe: generates n normals (rounded up to a multiple
  * of 128) -- positions 0 .. n/16 - 1 of each of the 16 streams seed ..
- * seed + 15, the 16 streams of a position together as the update generates
- * its members' noise -- and folds them into sink_dev[0] (one uint32,
- * overwritten) without other memory traffic: the generator's throughput
- * when nothing else runs. */
+ * seed + 15, the 16 streams of a position together, scaled and summed in
+ * fp64 as the update does with its members' noise -- and folds the sums into
+ * sink_dev[0] (one uint32, overwritten) without other memory traffic: the
+ * update's throughput when nothing else runs.  Perturbations round each
+ * normal to fp32, a few instructions more. */
 CPES_API int cpes_rng_probe(uint64_t seed, int64_t n, uint32_t* sink_dev, void* stream);
 
 /* Measurement references for the map and copy kernels: the same memory

@@ -1,7 +1,7 @@
 """The passes of the permutation partition at the sizes where they change:
 workgroups that share a tile (small partitions), the round-function tables
-(from 2^23 elements, one group of rounds in LDS per table size) and the 64-bit
-walk (above 2^32)."""
+(from 2^23 elements; as many rounds at a time as their tables fit the LDS) and
+the 64-bit walk (above 2^32)."""
 import numpy as np
 import pytest
 
@@ -62,15 +62,18 @@ def _check(T, d, K, wide, shift=0):
 @pytest.mark.parametrize("d,K,wide,shift", [
     (2047, 5, True, 0), (2048, 8, False, 0), (2049, 9, True, 0), (511, 33, False, 0), ((1 << 20) + 3, 64, True, 0),
     ((1 << 23) - 1, 8, True, 0),                                                            # one tile per workgroup
-    (1 << 23, 8, True, 0), ((1 << 23) + 1, 3, False, 1), ((1 << 24) + 1, 33, True, 1),     # all rounds in LDS
-    (1 << 26, 256, False, 3), ((1 << 26) + 1, 8, True, 0),                                  # h = 13, then four rounds
-    (1 << 28, 16, False, 0), ((1 << 28) + 1, 8, False, 0),                                  # then two
-    ((1 << 30) + 3, 7, False, 0),                                                           # then one
+    (1 << 23, 8, True, 0), ((1 << 23) + 1, 3, False, 1), ((1 << 24) + 1, 33, True, 1),     # all rounds' tables in LDS
+    (1 << 26, 256, False, 3),                                                               # the last such size
+    ((1 << 26) + 1, 8, True, 0), (1 << 28, 16, False, 0),                                   # h = 14: two rounds at a time
+    ((1 << 28) + 1, 8, False, 0), (1 << 30, 8, False, 1),                                   # h = 15: one, in half of the LDS
+    ((1 << 30) + 3, 7, False, 0), (1 << 32, 8, False, 0),                                   # h = 16: one, undoubled
 ])
 def test_map_matches_the_permutation(d, K, wide, shift):
     import torch as T
 
     _check(T, d, K, wide, shift)
+    if d >= 1 << 30:
+        T.cuda.empty_cache()
 
 
 @pytest.mark.gpu

@@ -1,6 +1,7 @@
 """The branches of the noise and copy kernels that neither length nor layout
 selects: streams whose coefficient is zero, noise blocks above 2^32, and
-ranges and side buffers that start at no vector boundary."""
+ranges and side buffers, on the device or the host, that start at no vector
+boundary."""
 import numpy as np
 import pytest
 
@@ -168,6 +169,49 @@ def test_any_element_alignment(orc, T, length, dtype, layout):
     for shift, side in ((1, 0), (0, 1), (3, 5), (7, 2)):
         for a, b in zip(want, passes(shift, side)):
             assert T.equal(a, b)
+
+
+@pytest.mark.parametrize("length", [1, 9, 2049, 70001])
+@pytest.mark.parametrize("dtype", [S.BF16, S.F32])
+@pytest.mark.parametrize("layout", ["contiguous", "chunk", "map", "ascending", "ascending32"])
+def test_host_backup_at_any_element(orc, T, length, dtype, layout):
+    """Backup to pinned host memory and restore from it with the weights and
+    the host buffer each at their own element offset from a vector boundary:
+    the host holds the bits that the subspace had, a restore brings them back,
+    and nothing around either range is written."""
+    C = 256
+    numel = 4 * length + 8 * C
+    base = S.host_weights(numel, dtype, length)
+    rng = np.random.default_rng(4)
+    if layout == "contiguous":
+        at, sub = np.arange(5, 5 + length), cp.subspace(5, length)
+    elif layout == "chunk":
+        chunks = rng.permutation(numel // C)[:length // C + 1].astype(np.int64)
+        at = (chunks[:, None] * C + np.arange(C)).reshape(-1)[:length]
+        sub = cp.subspace(0, length, to_dev(chunks), C)
+    else:
+        index = np.sort(rng.permutation(numel)[:length + 3])
+        at = index[3:]
+        sub = cp.subspace(3, length, to_dev(index.astype(np.int32 if layout == "ascending32" else np.int64)),
+                          ascending=layout != "map")
+    tdt = T.bfloat16 if dtype == S.BF16 else T.float32
+    w0 = to_dev(base)
+    for shift, side in ((0, 0), (1, 0), (0, 1), (3, 5), (7, 2)):
+        buf = T.zeros(numel + 16, dtype=tdt, device="cuda")
+        w = buf[shift:shift + numel]
+        w.copy_(w0)
+        host = T.full((length + 16,), 7, dtype=tdt, pin_memory=True)
+        hb = host[side:side + length]
+        cp.cpes_backup_to_host(w, sub, hb)
+        T.cuda.synchronize()
+        assert np.array_equal(to_host(hb), base[at])
+        assert bool((host[:side] == 7).all()) and bool((host[side + length:] == 7).all())
+        cp.cpes_perturb(w, sub, 0.5, 3, 1)
+        assert not bool(T.equal(w, w0))
+        cp.cpes_restore_from_host(w, sub, hb)
+        T.cuda.synchronize()
+        assert bool(T.equal(w, w0))
+        assert not bool(buf[:shift].any()) and not bool(buf[shift + numel:].any())
 
 
 @pytest.mark.parametrize("kind", ["contiguous", "map", "step"])

@@ -340,13 +340,15 @@ def graph_step_ms(W, cp, torch, P, cache, steps, fused=False):
 
 def rng_ceiling(cp, torch):
     """The generator alone (cpes_rng_probe): 2^32 normals, 16 streams per
-    position as the update generates them, folded into one word with no other
-    memory traffic; median of 9 launches."""
+    position scaled and summed in fp64 as the update does, folded into one word
+    with no other memory traffic; median of 9 launches.  A perturbation rounds
+    each normal to fp32 besides, so it stays further below this rate."""
     n = 1 << 32
     sink = torch.empty(1, dtype=torch.int32, device="cuda")
     ms = event_ms(torch, lambda: cp.cpes_rng_probe(7, n, sink), reps=9)
     return {"Gnormal/s": round(n / (ms * 1e-3) / 1e9, 1), "normals": n, "ms": round(ms, 4),
-            "kind": "cpes_rng_probe: Philox4x32-10 + Box-Muller, 16 streams per position, no memory traffic"}
+            "kind": "cpes_rng_probe: Philox4x32-10 + Box-Muller, 16 streams per position summed in fp64, no memory "
+                    "traffic"}
 
 
 def copy_ceilings(cp, torch, src, dst):
@@ -438,6 +440,23 @@ def measure(W, cp, torch, steps, warmup, graph, fused=False):
                 sizes=sizes, parts=parts, steps=steps, warmup=warmup)
 
 
+def update_normals(W, rnorm, sizes):
+    """Normals the updates of one step generate: positions times the streams
+    whose coefficient (the sum of sign * rnorm over the members sharing a
+    seed) is not zero, since the library generates no noise for the others (a
+    mirrored pair with equal rewards).  ``rnorm``: one row per update."""
+    ks = W.member_subspaces() if W.copes_step else None
+    total = 0
+    for t, k in enumerate(W.active):
+        it = 0 if W.copes_step else t
+        coef = {}
+        for i, (seed, sign) in enumerate(zip(W.member_seeds(it), W.signs)):
+            if ks is None or ks[i] == k:
+                coef[seed] = coef.get(seed, 0.0) + sign * float(rnorm[it][i])
+        total += sizes[k] * sum(not c == 0.0 for c in coef.values())
+    return total
+
+
 def op_table(W, M, fused, ceil):
     """Per kernel class: launches, average ms, algorithmic GB/s and fractions."""
     import synthetic as S
@@ -469,7 +488,8 @@ def op_table(W, M, fused, ceil):
         if op in ("perturb", "update"):
             streams = 1
             if op == "update":
-                streams = len(set(W.member_seeds(0))) // (W.K if W.copes_step else 1)
+                streams = update_normals(W, M["P"]["rnorm"].cpu().numpy(), M["sizes"]) / span
+                entry["streams_generated"] = round(streams, 2)
             gn = streams * per_launch / (avg_ms * 1e-3) / 1e9
             entry["params/s"] = round(per_launch / (avg_ms * 1e-3), 1)
             entry["Gnormal/s"] = round(gn, 2)
@@ -620,7 +640,7 @@ def kernels_once(cp, torch):
     sigma = W.sigma_k(4)
     seeds64 = [m + 1 for m in range(64) for _ in (0, 1)]
     signs64 = [1, -1] * 64
-    r128 = torch.from_numpy(S.rewards("mean_bernoulli", 128, 99)).to(dev)
+    r128 = torch.from_numpy(S.rewards("uniform", 128, 99)).to(dev)          # no pair cancels: 64 streams
     rn128 = torch.empty_like(r128)
     sink = torch.empty(1, dtype=torch.int32, device=dev)
     for _ in range(2):

@@ -37,6 +37,29 @@ def test_bytes_per_position(bench, name, op, expected):
     assert bench.bytes_per_position(S.workload(name), op) == pytest.approx(expected)
 
 
+@pytest.mark.parametrize("name", ["c1", "c2", "c5", "p0"])
+def test_update_normals_counts_the_streams_that_are_generated(bench, name):
+    """Normals of one step's updates: every member's own stream where none
+    cancels (c1, p0), and without the mirrored pairs of equal rewards (c2, c5:
+    a pair contributes only if its two rewards differ)."""
+    import oracle as O
+    import synthetic as S
+    O.build(force=False)
+    W = S.workload(name)
+    iters = range(1 if W.copes_step else len(W.active))
+    rnorm = [O.normalize(W.rewards(t), W.norm_mode)[0] for t in iters]
+    if name == "p0":
+        assert bench.update_normals(W, rnorm, W.sizes()) == 10 * W.d          # 40 members over 4 subspaces
+        return
+    want = 0
+    for t, k in enumerate(W.active):
+        r = W.rewards(t)
+        streams = sum(a != b for a, b in zip(r[::2], r[1::2])) if name in ("c2", "c5") else W.n
+        assert name == "c1" or 0 < streams < W.n // 2
+        want += streams * W.sizes()[k]
+    assert bench.update_normals(W, rnorm, W.sizes()) == want
+
+
 def test_extras_default_to_the_other_benchmark_workloads(bench):
     assert bench.parse([]).extras == ["c1", "c2", "c4", "c5"]
     assert bench.parse(["--workload", "c4"]).extras == []

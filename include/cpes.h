@@ -138,6 +138,8 @@ typedef struct cpes_subspace {
  *   by cycle-walking.  index_dev (device int64[d]) receives, for each k, the
  *   members of subspace k in ascending order at [offsets[k], offsets[k+1]),
  *   and offsets_host[k] = ceil(k d / K) (exact because E is a bijection).
+ *   While the call runs the map's memory also holds intermediate tables, so
+ *   its entries are undefined until it ends, also where the same map is replayed.
  *   Requires 1 <= K <= CPES_MAX_PERMUTATION_K, d < 2^55 and a device workspace of
  *   cpes_partition_workspace_bytes() bytes (16-byte aligned).
  * status_dev: NULL, or a device int32 set to 0, or to 1 if a cycle walk

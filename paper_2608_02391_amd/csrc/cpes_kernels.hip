@@ -1400,7 +1400,7 @@ __global__ __launch_bounds__(kBlock) void k_normalize_rank(NormalizeArgs a)
     }
 }
 
-// Groups and ranks in place, one workgroup.  The rewards are sorted in LDS by
+// Z-scores of groups and ranks in place, one workgroup.  The rewards are sorted in LDS by
 // the 64-bit key (group, value, index) -- the value as an order-preserving
 // 32-bit image of the fp32 bits, -0 taken as +0 -- with a bitonic network.
 // Each group is then one run of the sorted keys.  Z: one wave per group sums
@@ -1590,7 +1590,8 @@ template <int WPT> constexpr int kPartSub = (int)kTile / WPT;            // elem
 // Partitions of at least this many elements take the table path below: 2^22
 // elements take 47 us there and 66 us in k_part_bucket, but 2^22 + 5 (three
 // of four walks leave the range) 296 and 223 us; 2^23: 166 and 214 us,
-// 2^26: 341 and 720 us, 2^26 + 1: 1,790 and 2,590 us.
+// 2^26: 341 and 720 us, 2^26 + 1: 1,790 and 2,590 us, measured when the line
+// was drawn (the table path now takes 160, 285 and 1,330 us at the last three).
 constexpr int64_t kPartTableMin = 1ll << 23;
 
 // Pass 1: bucket of every element, and per-tile bucket counts.  Bound by the
@@ -1600,9 +1601,11 @@ constexpr int64_t kPartTableMin = 1ll << 23;
 // whose element has arrived in [0, d) takes the next one of the wave's range
 // at once, ranked among the lanes that finish with it.  Buckets are collected
 // in LDS (the elements of a lane are not consecutive) and written as 16-byte
-// vectors.  1,009,308,160 elements: 8.8 ms, where lanes walking in step (and a
-// 64-bit division per element) took 18.5 ms; 268,435,465 (three of four walks
-// leave the range): 10 ms against 36 ms.
+// vectors.  It serves partitions below kPartTableMin (X = uint32_t, WPT = 4)
+// and above 2^32 elements (X = uint64_t, WPT = 1), this pass alone: 2^22
+// elements 43 us and 2^22 + 5 (three of four walks leave the range) 238 us,
+// where lanes walking in step, a wave per tile and a 64-bit division per
+// element took 50 and 682 us; 2^32 + 5 elements 167 ms against 556 ms.
 template <typename X, int WPT>
 __global__ __launch_bounds__(64 * kPartWaves) void k_part_bucket(PartitionArgs a)
 {
@@ -2183,15 +2186,23 @@ int64_t grid_for(int64_t work_items, int64_t cap = kMaxGrid)
 }
 
 // Workgroups of a noise kernel on `items` units of a contiguous or chunked
-// subspace (threads of kBlock).  Up to 8,192 of them take one unit per thread.  Larger launches
-// loop: the tables are staged once per workgroup, so a workgroup wants several
-// units, but with few, long workgroups the launch ends on the slowest CU
-// (504,654,080 positions, 16 streams: 8,192 workgroups 6.64 ms, one workgroup
-// per four units of a thread 6.50 ms, per three 6.46 ms, per two 6.51 ms; one
-// perturbation 566, 558, 548 and 553 us).  The same rule serves perturbations
-// through ascending maps, in workgroups of two (126,163,520 positions, int64
-// map, from the backup, with its restore: 1,811 us with 4,096 workgroups of 512
-// threads, 1,755 us with one per three tiles of a wave, 1,774 us per eight).
+// subspace (threads of kBlock).  Up to 8,192 of them take one unit per thread.
+// Larger launches loop: the tables are staged once per workgroup, so a
+// workgroup wants several units, but with few, long workgroups the launch ends
+// on the slowest CU (504,654,080 positions, 16 streams: 8,192 workgroups 6.64
+// ms, one workgroup per four units of a thread 6.50 ms, per three 6.46 ms, per
+// two 6.51 ms; one perturbation 566, 558, 548 and 553 us).  Between 8,193 and
+// 24,576 workgroups' worth of units the grid stays at 8,192 and some threads
+// take a unit more than others; the same number of units for each is at most
+// 3 % faster and often slower (one bf16 perturbation in place, this rule, and
+// one, two, three units a thread: 9.4 M positions 13.0, 12.9, 12.8, 12.8 us;
+// 17 M 20.5, 20.6, 20.3, 19.8; 33.3 M 35.2, 36.1, 35.5, 36.6; 37.7 M 39.8,
+// 40.8, 40.0, 40.5; 50.4 M 52.1, 52.6, 53.5, 54.1; an update with 10 streams on
+// 17 M 143, 143, 148, 146, on 37.7 M 305, 302, 304, 304).  The same rule serves
+// perturbations through ascending maps, in workgroups of two (126,163,520
+// positions, int64 map, from the backup, with its restore: 1,811 us with 4,096
+// workgroups of 512 threads, 1,755 us with one per three tiles of a wave, 1,774
+// us per eight).
 int64_t noise_grid_cap(int64_t items)
 {
     const int64_t blocks = (items + kBlock - 1) / kBlock;

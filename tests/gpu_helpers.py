@@ -82,12 +82,14 @@ def bf16_close(got_bits, ref_bits) -> bool:
 
 def update_slack(orc, seeds, signs, rnorm, step, j) -> np.ndarray:
     """(n_streams + 2) 2^-24 |step| sum_u |c_u z_u(j)| at noise positions j:
-    how far the device's fp32 accumulation of an update (Eq. 13) can drift
-    from the oracle's fp64 one.  The device rounds each coefficient
-    c_u = sum of sign * rnorm over the members of stream u, and the step, to
-    fp32 (2^-24 relative each) and adds the n_streams products c_u z_u with
-    fused multiply-adds, each rounding the running sum once (at most
-    2^-24 sum_u |c_u z_u| each)."""
+    how far an fp32 accumulation of an update (Eq. 13) can drift from the
+    oracle's fp64 one: each coefficient c_u = sum of sign * rnorm over the
+    members of stream u, and the step, rounded to fp32 (2^-24 relative each)
+    and the n_streams products c_u z_u added with fused multiply-adds, each
+    rounding the running sum once (at most 2^-24 sum_u |c_u z_u| each).  The
+    device needs a small part of it: it sums unrounded normals in fp64, where
+    the oracle rounds each to fp32 (2^-25 sum_u |c_u z_u| in all), and rounds
+    the sum and the step once."""
     coef = {}
     for sd, sg, r in zip(seeds, signs, rnorm):
         coef[int(sd)] = coef.get(int(sd), 0.0) + float(sg) * float(r)
@@ -109,7 +111,7 @@ def bf16_update_close(got_bits, ref_bits, slack_at) -> bool:
         |got - ref| <= ulp_bf16(max(|got|, |ref|)) + 2^-23 |ref| + slack_at(k).
     The first term is the two roundings to bf16, the second the two fp32
     roundings before them, and slack_at(k) (update_slack at element k's noise
-    position) the fp32 accumulation.  slack_at is only evaluated at the
+    position) the accumulation in fp32.  slack_at is only evaluated at the
     elements the first two terms do not cover."""
     g = bf16_value(got_bits).astype(np.float64)
     r = bf16_value(ref_bits).astype(np.float64)
@@ -132,8 +134,8 @@ def zscore_close(got, ref, r, group=None) -> bool:
         |got - ref| <= ulp32(ref) + 2 (c + 8) 2^-53 ((1 + |z|) A / s + |z|),
     with c the size, A the mean |r| and s the population standard deviation of
     the element's group (fp64), z = ref.  The oracle sums each group
-    sequentially, the device in another fixed order (64 lane-strided partial
-    sums and a butterfly); each fp64 sum of c terms is within (c - 1) 2^-53 A c
+    sequentially, the device in another fixed order (strided partial sums per
+    lane, a butterfly over the wave, the waves in order); each fp64 sum of c terms is within (c - 1) 2^-53 A c
     of the exact one, so the means differ by at most about 2 (c + 8) 2^-53 A
     and the deviations' relative error is about as large.  Carried through
     (r - mu) / s that bounds the fp64 quotients' difference, and the rounding

@@ -71,3 +71,41 @@ def test_captured_step_replays_match_eager(layout):
         junk = T.randn(1 << 20, device=dev) * 2      # unrelated eager work between replays
         del junk
         T.cuda.synchronize()
+
+
+def test_captured_step_update_with_every_member_and_subspace():
+    """The whole-step update at its limits (256 members, 32 subspaces), whose
+    kernel arguments exceed 4 KiB: each replay equals the eager call, and the
+    last member counts."""
+    T = torch()
+    K, n = cp.MAX_STEP_SUBSPACES, cp.MAX_MEMBERS
+    d = K * 5000 + 3
+    offs = cp.cpes_partition(cp.PART_CONTIGUOUS, d, K)
+    seeds, signs, ks = list(range(1, n + 1)), [1 - 2 * (i % 2) for i in range(n)], [i % K for i in range(n)]
+    rnorm = T.from_numpy(np.random.default_rng(6).normal(size=n).astype(np.float32)).cuda()
+    step = lambda w, r: cp.cpes_update_step(w, offs, seeds, signs, ks, r, 0.01, [1.0] * K, cp.SCALE_ALPHA_OVER_N)
+    w0 = S.device_weights(d, S.F32, 3)
+    ref, refs = w0.clone(), []
+    for _ in range(3):
+        step(ref, rnorm)
+        refs.append(ref.clone())
+    without_last = rnorm.clone()
+    without_last[-1] = 0.0
+    other = w0.clone()
+    step(other, without_last)
+    T.cuda.synchronize()
+    k = ks[-1]                                          # only the last member's subspace tells the two apart
+    assert not T.equal(other[offs[k]:offs[k + 1]], refs[0][offs[k]:offs[k + 1]])
+    assert T.equal(other[:offs[k]], refs[0][:offs[k]]) and T.equal(other[offs[k + 1]:], refs[0][offs[k + 1]:])
+
+    w = w0.clone()
+    g = T.cuda.CUDAGraph()
+    with T.cuda.graph(g):
+        step(w, rnorm)
+    for r in range(3):
+        g.replay()
+        T.cuda.synchronize()
+        assert T.equal(w, refs[r]), f"replay {r}"
+        junk = T.randn(1 << 20, device="cuda") * 2      # unrelated eager work between replays
+        del junk
+        T.cuda.synchronize()
